@@ -548,6 +548,10 @@ __device__ __forceinline__ void solve_small(int c, int b, const float* __restric
 #pragma unroll
     for (int i = 0; i < PT; ++i)
       if (tid + kThreads * i < NE) mine[tid + kThreads * i] = g[i];
+    // Every wave waits until its stores have reached the L2: the barrier does not (it is enough for
+    // the waves of one CU, which share a vector cache), and the write-back below waits for its own
+    // wave's only, while the reader may run on another XCD, behind another L2.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     // one thread releases the workgroup's partial and acquires the others' (every wave doing so
     // took 7 us); the count returns to zero for the next launch
