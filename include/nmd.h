@@ -238,9 +238,10 @@ int nmd_run_steps(nmd_ctx* ctx, float* W, float* H, const int32_t* steps, int32_
  * 4.2), and the second product is skipped on every slice of 16 rows x 4 panel rows (r <= 64: 32
  * rows x 16 panel rows) where S-hat is zero (Sec. 4.3).  r must be 16, 32, 48, 64 or a multiple of 64 up to 512; rows >= 1 and
  * <= 2^31 - 1, blk >= 1.  Padding columns of A and B must hold zeros.  fp32 accumulation
- * over all of B; at r <= 64 both products run on f16 MFMA of two-term splits, with errors
- * against fp64 no larger than the fp32 products' (rows of A or a B with infinities or NaN: plain
- * fp32).  Asynchronous on hip_stream; allocates nothing.  NMD_EINVAL on bad arguments,
+ * over all of B; at r <= 64 both products run on bf16 MFMA of three-term splits that hold every
+ * operand whole (x = h + m + l, 24 bits; six products each), within the error bounds of fp32
+ * products and sums.  Rows of A and panels with infinities, NaN or nonzero magnitudes outside
+ * [2^-108, 2^127) take plain fp32, more slowly.  Asynchronous on hip_stream; allocates nothing.  NMD_EINVAL on bad arguments,
  * NMD_EDEVICE if the launch fails.
  */
 int nmd_rectified_contraction(const float* A, int64_t rows, const float* B, int64_t blk,

@@ -1,44 +1,39 @@
-// The dense contraction Y = sgn max(0, X P^T) P at r_p <= 64, both products on f16 MFMA of
-// two-term splits at fp32 accuracy.
+// The dense contraction Y = sgn max(0, X P^T) P at r_p <= 64, both products on bf16 MFMA of
+// three-term splits (split3.h), which hold every operand whole.
 //
-// A wave holds 32 rows of X as split operands (scaled per row as in split_f16.h) and takes the
-// panel 32 rows at a time: L^T = P X^T as 32 x 32 tiles, so that a lane's sixteen entries of L
-// belong to one row of X and are, in pairs of registers, already the operand of the second
-// product Y^T += P^T max(0, L)^T.  The rectified entries are split again: they are scaled by a
-// power of two per row of X that keeps the largest seen so far below 2^16 (when a larger one
-// comes, the row's sums are scaled down with it, exactly), so that hi + lo keeps 22 bits of every
-// entry within 2^-14 of the largest and 2^-40 of the largest below that.  Both products are
-// hi hi + (hi lo + lo hi), the small terms in accumulators of their own.
+// A wave holds 32 rows of X as split operands and takes the panel 32 rows at a time: L^T = P X^T
+// as 32 x 32 tiles, so that a lane's sixteen entries of L belong to one row of X and are, in pairs of
+// registers, already the operand of the second product Y^T += P^T max(0, L)^T.  The rectified
+// entries, fp32 as they come, are split again.  Both products keep the small terms in accumulators
+// of their own.
 //
 // The workgroup's eight waves share the panel through LDS: each thread reads four fp32 values
-// a block ahead, scales and splits them and writes them row-major to the other buffer.  The first
-// product reads the rows as they lie, the second reads them transposed (ds_read_b64_tr_b16),
-// so there is one copy and no pass over the panel before the launch.  Rows are padded by 16 bytes:
-// sixteen rows' 16-byte chunks fall on distinct banks.
+// a block ahead, splits them and writes them row-major to the other buffer.  The first product
+// reads the rows as they lie, the second reads them transposed (ds_read_b64_tr_b16), so there is
+// one copy and no pass over the panel before the launch.  Rows are padded by 16 bytes: sixteen rows'
+// 16-byte chunks fall on distinct banks.
 //
-// What bounds it: at r_p = 64 the f16 matrix rate and the vector work beside it (about 130
-// vector instructions per wave and 32 x 32 tile, beside 24 MFMAs); at r_p = 16 the vector work.
-// 250000 x 2500, r = 64, half of L positive: 0.55 ms, 290 TFLOP/s of the two products (870 of f16);
-// the fp32 kernel before it 1.22 ms (131).  60000 x 8192, r = 48 / 32 / 16: 0.42 / 0.29 / 0.20 ms
-// against 0.75 / 0.53 / 0.31.  4096 x 4096, r = 16, 16 ranges: 16 us against 28.  The sums of the
-// second product are taken in chains of kChain panel rows: error against fp64 at 250000 x 2500
-// 8.1e-8 (2.7e-7 and 0.54 ms as one chain; the fp32 kernel 5.3e-7), and a fit does not need more
-// ranges than fill the chip for its accuracy.
+// What bounds it: the bf16 matrix rate and the vector work beside it (48 MFMAs a wave and 32 x 32 tile
+// at r_p = 64); at r_p = 16 the vector work.  250000 x 2500, r = 64, half of L positive: 0.76 ms, 210
+// TFLOP/s of the two products (1260 of bf16), against 1.21 ms of fp32 MFMA; 60000 x 8192, r = 48 / 32 /
+// 16 0.54 / 0.34 / 0.26 ms against 0.82 / 0.58 / 0.37.  Two-term f16 splits with a scale per row took
+// 0.55 ms at the first shape, but lost columns far below their row's largest (10^-2 of a column of Y at
+// 2^-32) and the last bit of a quarter of the values.  The sums of the second product are taken in
+// chains of kChain panel rows.  Error against fp64 at the first shape 5.9e-8 (fp32 MFMA: 5.2e-7).
 //
-// A workgroup whose rows or panel hold an infinity or NaN computes its rows again in plain fp32.
+// A workgroup whose rows or panel range hold an infinity, a NaN or a magnitude outside the splits'
+// range, or whose sums overflow, computes its rows again in plain fp32.
 
-#include "split_f16.h"
+#include "split3.h"
 
 namespace nmd {
 namespace fs {
 
-using fx::floatx16;
-using fx::mfma;
-using fx::u32x4;
+using s3::floatx16;
+using s3::mfma;
+using s3::u32x2;
+using s3::u32x4;
 typedef short short4v __attribute__((ext_vector_type(4)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
 template <int RP_>
 struct Cfg {
@@ -50,39 +45,13 @@ struct Cfg {
   static constexpr int KC = RP / 16;                            // k chunks of the first product
   static constexpr int MT = (RP + 31) / 32;                     // column tiles of Y
   static constexpr int STR = 2 * RP + 16;                       // bytes of a row in LDS
-  static constexpr int PLANE = JB * STR;                        // hi or lo
-  static constexpr int BUF = 2 * PLANE + 4 * JB;                // and the row scales
+  static constexpr int PLANE = JB * STR;                        // one term of the block
+  static constexpr int BUF = 3 * PLANE;
   // registers of a column tile that hold columns of Y (half of the last tile's at 16 and 48)
   static constexpr int cols(int mt) { return 32 * mt + 16 < RP ? 16 : 8; }
 };
 
-constexpr float kLimit = 60000.f;  // of a scaled entry (f16: 65504)
-constexpr int kTop = 12;           // a rescaled row's largest entry is below 2^kTop
-constexpr int kChain = 256;        // panel rows per accumulator chain of the second product
-
-__device__ __forceinline__ void split2(float a, float b, unsigned& hi, unsigned& lo) {
-  const float2v x = {a, b};
-  const half2v h = __builtin_convertvector(x, half2v);
-  const float2v d = {a - (float)h[0], b - (float)h[1]};
-  hi = __builtin_bit_cast(unsigned, h);
-  lo = __builtin_bit_cast(unsigned, __builtin_convertvector(d, half2v));
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_max(float x) {
-  const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true);
-  return fmaxf(x, __builtin_bit_cast(float, y));
-}
-
-// Largest over the LPR lanes that hold a row.
-template <int LPR>
-__device__ __forceinline__ float row_max(float x) {
-  x = dpp_max<0xB1>(x);                          // quad_perm 1 0 3 2
-  x = dpp_max<0x4E>(x);                          // quad_perm 2 3 0 1
-  if constexpr (LPR >= 8) x = dpp_max<0x141>(x);  // row_half_mirror
-  if constexpr (LPR >= 16) x = dpp_max<0x140>(x); // row_mirror
-  return x;
-}
+constexpr int kChain = 256;  // panel rows per accumulator chain of the second product
 
 // Four columns of 4 consecutive panel rows transposed: lane (l % 16) of a 16-lane group names four
 // halves of row (l % 16) / 4 and receives the four rows' halves of column l % 16.
@@ -103,30 +72,28 @@ __device__ __forceinline__ float4 fetch(const float* __restrict__ P, int64_t j0,
 }
 
 template <int RP>
-__device__ __forceinline__ void stash(char* buf, float4 v, float& nonfinite, int tid) {
+__device__ __forceinline__ void stash(char* buf, float4 v, s3::Range& range, int tid) {
   using C = Cfg<RP>;
   const int j = tid / C::LPR, g = tid % C::LPR;
-  nonfinite = fmaf(v.x, 0.f, fmaf(v.y, 0.f, fmaf(v.z, 0.f, fmaf(v.w, 0.f, nonfinite))));
-  const float amax =
-      row_max<C::LPR>(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-  const int e = fx::scale_exp(amax);
-  u32x2 hi, lo;
-  unsigned a, b;
-  split2(ldexpf(v.x, e), ldexpf(v.y, e), a, b);
-  hi[0] = a;
-  lo[0] = b;
-  split2(ldexpf(v.z, e), ldexpf(v.w, e), a, b);
-  hi[1] = a;
-  lo[1] = b;
+  range.see(v.x);
+  range.see(v.y);
+  range.see(v.z);
+  range.see(v.w);
+  u32x2 t[3];
+  unsigned h, m, l;
+  s3::split(v.x, v.y, h, m, l);
+  t[0][0] = h; t[1][0] = m; t[2][0] = l;
+  s3::split(v.z, v.w, h, m, l);
+  t[0][1] = h; t[1][1] = m; t[2][1] = l;
   if (4 * g < RP) {
-    *reinterpret_cast<u32x2*>(buf + j * C::STR + 8 * g) = hi;
-    *reinterpret_cast<u32x2*>(buf + C::PLANE + j * C::STR + 8 * g) = lo;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *reinterpret_cast<u32x2*>(buf + k * C::PLANE + j * C::STR + 8 * g) = t[k];
   }
-  if (g == 0) reinterpret_cast<int*>(buf + 2 * C::PLANE)[j] = -2 * e;
 }
 
-// The workgroup's rows in plain fp32, for inputs that are not finite.  Entries of L that are not
-// above zero (NaN included) add nothing.
+// The workgroup's rows in plain fp32, for inputs outside the splits' range.  Entries of L that are
+// not above zero (NaN included) add nothing.
 template <int RP>
 __device__ __noinline__ void plain_rows(const float* __restrict__ X, int64_t rows,
                                         const float* __restrict__ P, int64_t jb0, int64_t jb1,
@@ -171,42 +138,30 @@ __global__ __launch_bounds__(512, RP <= 16 ? 4 : 2) void dense_small_kernel(
   const int64_t row = row0 + 32 * wave + l32;
 
   float4 next = fetch<RP>(P, jb0, jb1, tid);
-  float nonfinite = 0.f;
+  s3::Range range;
   if (tid == 0) bad = 0, total = 0;
 
   // the wave's rows of X: lane (h, l32) holds row l32, columns 16 t + 8 h .. + 7 of chunk t
-  u32x4 xh[C::KC], xl[C::KC];
-  int ex;
-  {
-    float x[C::KC][8];
-    float amax = 0.f;
+  u32x4 xh[C::KC], xm[C::KC], xl[C::KC];
 #pragma unroll
-    for (int t = 0; t < C::KC; ++t) {
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-      if (row < rows) {
-        const float* src = X + row * RP + 16 * t + 8 * h;
-        a = *reinterpret_cast<const float4*>(src);
-        b = *reinterpret_cast<const float4*>(src + 4);
-      }
-      x[t][0] = a.x; x[t][1] = a.y; x[t][2] = a.z; x[t][3] = a.w;
-      x[t][4] = b.x; x[t][5] = b.y; x[t][6] = b.z; x[t][7] = b.w;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        amax = fmaxf(amax, fabsf(x[t][e]));
-        nonfinite = fmaf(x[t][e], 0.f, nonfinite);
-      }
+  for (int t = 0; t < C::KC; ++t) {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    if (row < rows) {
+      const float* src = X + row * RP + 16 * t + 8 * h;
+      a = *reinterpret_cast<const float4*>(src);
+      b = *reinterpret_cast<const float4*>(src + 4);
     }
-    amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
-    ex = fx::scale_exp(amax);
+    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-    for (int t = 0; t < C::KC; ++t)
+    for (int e = 0; e < 8; ++e) range.see(x[e]);
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        unsigned hi, lo;
-        split2(ldexpf(x[t][2 * w], ex), ldexpf(x[t][2 * w + 1], ex), hi, lo);
-        xh[t][w] = hi;
-        xl[t][w] = lo;
-      }
+    for (int w = 0; w < 4; ++w) {
+      unsigned s0, s1, s2;
+      s3::split(x[2 * w], x[2 * w + 1], s0, s1, s2);
+      xh[t][w] = s0;
+      xm[t][w] = s1;
+      xl[t][w] = s2;
+    }
   }
 
   // register 4 t + v of tile mt is column 32 mt + 8 t + 4 h + v; ys: the sums of yh, which starts
@@ -218,14 +173,13 @@ __global__ __launch_bounds__(512, RP <= 16 ? 4 : 2) void dense_small_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) yh[mt][v] = yl[mt][v] = ys[mt][v] = 0.f;
   int chain = 0;
-  int cx = 1000;  // scale exponent of the lane's row in the second product; the first entry lowers it
   unsigned slices = 0;
 
-  stash<RP>(smem, next, nonfinite, tid);
+  stash<RP>(smem, next, range, tid);
   next = fetch<RP>(P, jb0 + C::JB, jb1, tid);
-  fx::consumer_barrier();
+  s3::lds_barrier();
 
-  // this lane's offsets in a block: its row of the first product, its four halves of the second
+  // this lane's offsets in a block: its row of the first product, its four entries of the second
   // (at r_p = 16 and 48 the last tile's upper columns repeat the lower: their sums are not stored)
   const int at1 = l32 * C::STR + 16 * h;
   const int at2 = (4 * h + ((lane & 15) >> 2)) * C::STR + 8 * (lane & 3);
@@ -235,57 +189,34 @@ __global__ __launch_bounds__(512, RP <= 16 ? 4 : 2) void dense_small_kernel(
   for (int64_t j0 = jb0; j0 < jb1; j0 += C::JB) {
     const char* buf = smem + cur * C::BUF;
     if (j0 + C::JB < jb1) {
-      stash<RP>(smem + (cur ^ 1) * C::BUF, next, nonfinite, tid);
+      stash<RP>(smem + (cur ^ 1) * C::BUF, next, range, tid);
       next = fetch<RP>(P, j0 + 2 * C::JB, jb1, tid);
     }
     const int64_t left = jb1 - j0;
     const int subs = left >= C::JB ? C::JB / 32 : (int)((left + 31) / 32);
     for (int sub = 0; sub < subs; ++sub) {
       const char* tile = buf + 32 * sub * C::STR;
-      const int4* qs = reinterpret_cast<const int4*>(buf + 2 * C::PLANE) + 8 * sub + h;
       floatx16 acc, low;
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] = low[v] = 0.f;
 #pragma unroll
       for (int t = 0; t < C::KC; ++t) {
         const u32x4 ph = *reinterpret_cast<const u32x4*>(tile + at1 + 32 * t);
-        const u32x4 pl = *reinterpret_cast<const u32x4*>(tile + C::PLANE + at1 + 32 * t);
+        const u32x4 pm = *reinterpret_cast<const u32x4*>(tile + C::PLANE + at1 + 32 * t);
+        const u32x4 pl = *reinterpret_cast<const u32x4*>(tile + 2 * C::PLANE + at1 + 32 * t);
         acc = mfma(ph, xh[t], acc);
         low = mfma(ph, xl[t], low);
         low = mfma(pl, xh[t], low);
+        low = mfma(pm, xm[t], low);
+        low = mfma(ph, xm[t], low);
+        low = mfma(pm, xh[t], low);
       }
-      int q[16];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int4 w = qs[2 * t];
-        q[4 * t] = w.x; q[4 * t + 1] = w.y; q[4 * t + 2] = w.z; q[4 * t + 3] = w.w;
-      }
-      // u: entries of max(0, L), scaled; register 4 t + v is panel row 8 t + 4 h + v
+      // u: entries of max(0, L); register 4 t + v is panel row 8 t + 4 h + v
       float u[16], top[2] = {0.f, 0.f};
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        acc[v] += low[v];
-        u[v] = fmaxf(ldexpf(acc[v], q[v] + cx), 0.f);
+        u[v] = fmaxf(acc[v] + low[v], 0.f);
         top[v >> 3] = fmaxf(top[v >> 3], u[v]);
-      }
-      if (__any(fmaxf(top[0], top[1]) > kLimit)) {
-        int em = -100000;
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (acc[v] > 0.f) em = max(em, __builtin_amdgcn_frexp_expf(acc[v]) + q[v]);
-        em = max(em, __shfl_xor(em, 32, 64));
-        const int to = min(cx, kTop - em);
-#pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            yh[mt][v] = ldexpf(yh[mt][v], to - cx);
-            yl[mt][v] = ldexpf(yl[mt][v], to - cx);
-            if (v < C::cols(mt)) ys[mt][v] = ldexpf(ys[mt][v], to - cx);
-          }
-        cx = to;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) u[v] = fmaxf(ldexpf(acc[v], q[v] + cx), 0.f);
       }
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -293,24 +224,30 @@ __global__ __launch_bounds__(512, RP <= 16 ? 4 : 2) void dense_small_kernel(
         const unsigned long long live = __ballot(top[c] > 0.f);
         if (live == 0) continue;
         slices += 4u * (((live & 0x0000ffff0000ffffull) != 0) + ((live & 0xffff0000ffff0000ull) != 0));
-        u32x4 zh, zl;
+        u32x4 zh, zm, zl;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          unsigned hi, lo;
-          split2(u[8 * c + 2 * w], u[8 * c + 2 * w + 1], hi, lo);
-          zh[w] = hi;
-          zl[w] = lo;
+          unsigned s0, s1, s2;
+          s3::split(u[8 * c + 2 * w], u[8 * c + 2 * w + 1], s0, s1, s2);
+          zh[w] = s0;
+          zm[w] = s1;
+          zl[w] = s2;
         }
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt) {
           const char* p = tile + at2 + 16 * c * C::STR + 64 * mt + (32 * mt + 16 < RP ? up : 0);
-          const u32x2 h0 = read_tr(p), h1 = read_tr(p + 8 * C::STR);
-          const u32x2 l0 = read_tr(p + C::PLANE), l1 = read_tr(p + C::PLANE + 8 * C::STR);
-          const u32x4 ph = {h0[0], h0[1], h1[0], h1[1]};
-          const u32x4 pl = {l0[0], l0[1], l1[0], l1[1]};
-          yh[mt] = mfma(ph, zh, yh[mt]);
-          yl[mt] = mfma(ph, zl, yl[mt]);
-          yl[mt] = mfma(pl, zh, yl[mt]);
+          u32x4 q[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const u32x2 a = read_tr(p + k * C::PLANE), b = read_tr(p + k * C::PLANE + 8 * C::STR);
+            q[k] = u32x4{a[0], a[1], b[0], b[1]};
+          }
+          yh[mt] = mfma(q[0], zh, yh[mt]);
+          yl[mt] = mfma(q[0], zl, yl[mt]);
+          yl[mt] = mfma(q[2], zh, yl[mt]);
+          yl[mt] = mfma(q[1], zm, yl[mt]);
+          yl[mt] = mfma(q[0], zm, yl[mt]);
+          yl[mt] = mfma(q[1], zh, yl[mt]);
         }
       }
     }
@@ -325,11 +262,19 @@ __global__ __launch_bounds__(512, RP <= 16 ? 4 : 2) void dense_small_kernel(
         }
     }
     cur ^= 1;
-    fx::consumer_barrier();
+    s3::lds_barrier();
   }
 
   float* Y = Ypart + (int64_t)s * y_stride;
-  if (nonfinite != 0.f) bad = 1;  // only a NaN differs from zero here
+  bool again = range.outside();
+#pragma unroll
+  for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+    for (int v = 0; v < C::cols(mt); ++v) {
+      ys[mt][v] = sgn * (ys[mt][v] + (yh[mt][v] + yl[mt][v]));
+      again |= !isfinite(ys[mt][v]);
+    }
+  if (again) bad = 1;
   if (lane == 0 && slices) atomicAdd(&total, slices);
   __syncthreads();
   if (bad) {
@@ -339,14 +284,9 @@ __global__ __launch_bounds__(512, RP <= 16 ? 4 : 2) void dense_small_kernel(
     for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        if (32 * mt + 8 * t < RP) {
-          float o[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            o[v] = sgn * ldexpf(ys[mt][4 * t + v] + (yh[mt][4 * t + v] + yl[mt][4 * t + v]), -ex - cx);
+        if (32 * mt + 8 * t < RP)
           *reinterpret_cast<float4*>(Y + row * RP + 32 * mt + 8 * t + 4 * h) =
-              make_float4(o[0], o[1], o[2], o[3]);
-        }
+              make_float4(ys[mt][4 * t], ys[mt][4 * t + 1], ys[mt][4 * t + 2], ys[mt][4 * t + 3]);
   }
   if (counts && tid == 0 && total) atomicAdd(counts, (unsigned long long)total);
 }

@@ -115,7 +115,7 @@ struct nmd_ctx {
   int64_t g2_total = 0;              // slices examined (host count)
   int64_t dense_slots = 0;           // dense workgroups resident at once (CUs x per CU)
   int64_t dense_rows = 0;            // rows of X per dense workgroup
-  bool dense_small = false;          // the r_p <= 64 split-f16 kernel
+  bool dense_small = false;          // the r_p <= 64 split kernel
   int f16_wgs = 0;                   // split-f16 workgroups per CU; 0: another dense kernel
   hipStream_t side = nullptr;     // Gram and inverse run here, beside the contraction
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;

@@ -76,8 +76,8 @@ hipError_t launch_bf16x3_staged(const float* X, int64_t rows, const float* P, in
                                 float* work, float* Ypart, int64_t y_stride, int nsplit,
                                 float sgn, unsigned long long* live, hipStream_t st);
 
-// The same product (as launch_dense) at rp = 16, 32, 48, 64: both products on f16 MFMA of two-term
-// splits at fp32 accuracy (dense_small.hip); counts[0] receives 4 for every 16 rows x 16 panel
+// The same product (as launch_dense) at rp = 16, 32, 48, 64: both products on bf16 MFMA of
+// three-term splits (dense_small.hip); counts[0] receives 4 for every 16 rows x 16 panel
 // rows of max(0, L) with a positive entry.
 int dense_small_rows_per_wg();
 hipError_t dense_small_wgs_per_cu(int rp, int* out);
