@@ -28,7 +28,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA = 157.3   # TFLOP/s, MI355X dense fp32 matrix
-PEAK_BF16_MFMA = 2500.0  # TFLOP/s, MI355X dense bf16 (and f16) matrix
+PEAK_BF16_MFMA = 2500.0  # TFLOP/s, MI355X dense bf16 matrix
 PEAK_HBM = 8.0e3         # GB/s, MI355X HBM3E
 
 METRIC = "ALS sweeps/sec and dense-equiv TFLOP/s (4mnr/sweep), % of fp32 MFMA peak"
@@ -38,18 +38,18 @@ METRIC = "ALS sweeps/sec and dense-equiv TFLOP/s (4mnr/sweep), % of fp32 MFMA pe
 # kernel sources it was taken on.
 _CSRC = os.path.join(ROOT, "paper_2608_21607_amd", "csrc")
 _SPLIT_SOURCES = ("tile.h", "dense_kernel.h", "dense_bf16.h", "dense_bf16.hip", "dense_bf16_large.hip")
-_F16_SOURCES = ("tile.h", "split_f16.h", "dense_f16.hip")
+_DEFAULT_SOURCES = ("tile.h", "dense_kernel.h", "split3.h", "split_wide.h", "dense_split.hip")
 # (variant, workload) -> counter summary, and the sources of the dense kernel it measured
 TRAFFIC_FILES = {
-    ("fp32", 4): os.path.join(ROOT, "profiles", "f16_r256_graph139255_traffic.json"),
+    ("fp32", 4): os.path.join(ROOT, "profiles", "split3_r256_graph139255_traffic.json"),
     ("split_bf16", 4): os.path.join(ROOT, "profiles", "bf16x3_r256_graph139255_traffic.json"),
-    ("fp32", 5): os.path.join(ROOT, "profiles", "f16_r512_cooc500000x50000_traffic.json"),
+    ("fp32", 5): os.path.join(ROOT, "profiles", "split3_r512_cooc500000x50000_traffic.json"),
     ("split_bf16", 5): os.path.join(ROOT, "profiles", "bf16x3_r512_cooc500000x50000_traffic.json"),
 }
 KERNEL_SOURCES = {
-    ("fp32", 4): [os.path.join(_CSRC, f) for f in _F16_SOURCES],
+    ("fp32", 4): [os.path.join(_CSRC, f) for f in _DEFAULT_SOURCES],
     ("split_bf16", 4): [os.path.join(_CSRC, f) for f in _SPLIT_SOURCES],
-    ("fp32", 5): [os.path.join(_CSRC, f) for f in _F16_SOURCES],
+    ("fp32", 5): [os.path.join(_CSRC, f) for f in _DEFAULT_SOURCES],
     ("split_bf16", 5): [os.path.join(_CSRC, f) for f in _SPLIT_SOURCES],
 }
 
@@ -139,7 +139,7 @@ def kernel_mb(steps, warmup):
         res.append(row)
     return {"metric": "fused rectified contraction TFLOP/s (4 rows blk r per launch)",
             "unit": "TFLOP/s",
-            "dtype": "f32 (products of f16 splits at r <= 64); bf16x3 split for the bf16x3 columns",
+            "dtype": "f32 (three-term bf16 products at r <= 64); bf16x3 split for the bf16x3 columns",
             "data": "synthetic",
             "config": {"workload": "kernel alone, A 250000 x r, B 2500 x r, N(0,1)"},
             "steps": steps, "warmup": warmup, "results": res}
@@ -315,10 +315,10 @@ def main():
     dense_tflops = dense_alg_flops / dense_s / 1e12 if dense_s > 0 else 0.0
     dense_equiv_kernel = dense["flops"] / dense_s / 1e12 if dense_s > 0 else 0.0
     sparse_gbs = sparse["bytes"] / (sparse["ms"] / 1e3) / 1e9 if sparse["ms"] > 0 else 0.0
-    # Every algorithmic flop costs three bf16 flops with the split option and three f16 flops
-    # without it (at r_p >= 128 the second product's few entries run on fp32 MFMA), so the
-    # roofline peak is a third of the 16-bit MFMA peak.
-    peak = PEAK_BF16_MFMA / 3.0
+    # Every algorithmic flop costs three bf16 flops with the split option and six without it (at
+    # r_p >= 128 the second product's few entries run on fp32 MFMA), so the roofline peak is a
+    # third or a sixth of the bf16 MFMA peak.
+    peak = PEAK_BF16_MFMA / (3.0 if split else 6.0)
 
     out = {
         "metric": METRIC,
@@ -331,7 +331,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "bf16x3 split / f32" if split else "f32 (products of f16 splits)",
+        "dtype": "bf16x3 split / f32" if split else "f32 (three-term bf16 products)",
         "data": "synthetic",
         "config": {
             "workload": p.name + {
@@ -373,7 +373,7 @@ def main():
             "traffic": measured_traffic(args.config, "split_bf16" if split else "fp32"),
             "kernel": ((f"bxl_kernel<{rp}>" if rp >= 256 else f"bx32_kernel<{rp}>")
                        if split else
-                       f"dense_f16_kernel<{rp}>" if rp >= 128 else f"dense_small_kernel<{rp}>"),
+                       f"dense_split_kernel<{rp}>" if rp >= 128 else f"dense_small_kernel<{rp}>"),
             "launches": dense["launches"],
             "avg_launch_ms": dense["ms"] / max(1, dense["launches"]),
             "flops_per_launch": dense_alg_flops / max(1, dense["launches"]),

@@ -57,9 +57,12 @@ enum {
                           L = A B_J^T and max(0, L) B_J, run on bf16 MFMA with every
                           operand split in two (x = bf16(x) + bf16(x - bf16(x)), three
                           products each, fp32 accumulation; relative error about 2^-16 of
-                          the sum of the magnitudes of the terms) instead of fp32 MFMA, the
-                          counterpart of the paper's TF32 kernels (Sec. 4.2); the kernel of
-                          nmd_rectified_contraction_bf16x3.  Everything else stays fp32.
+                          the sum of the magnitudes of the terms), the counterpart of the
+                          paper's TF32 kernels (Sec. 4.2); the kernel of
+                          nmd_rectified_contraction_bf16x3.  Without it, and everywhere else,
+                          operands keep their 24 bits: products run on fp32 MFMA, or on bf16
+                          MFMA of three terms that hold an operand whole (six products), at
+                          fp32 accuracy.
                           Needs nmd_bf16x3_workspace_floats(max(m, n), r_p) floats more
                           device memory.  It adds one small kernel per step, so on steps
                           too small to fill the GPU it can cost more than it saves         */
@@ -292,7 +295,8 @@ int64_t nmd_bf16x3_workspace_floats(int64_t blk, int32_t r);
  * positive entry is skipped and the others run their own MFMAs (at r_p <= 64 by 32 rows x 16
  * panel rows, counted as the four slices of each 16 rows with a positive entry); at r_p >= 128
  * the second product instead runs per quad-column (4 rows x 1 panel row) holding a positive
- * entry.  *run = slices that ran whole, *total = slices examined, *entries = positive entries
+ * entry, except that at r_p other than 256 and 512 rows where much of L is positive run by slices.
+ * *run = slices that ran whole, *total = slices examined, *entries = positive entries
  * taken by quad-columns (r_p >= 128; with the split-bf16 option r_p = 256, 512); the second
  * product's useful work is run/total of its dense count plus 2 r flops per entry.  Synchronises the device.
  * reset != 0 clears all three after reading.  Any output pointer may be NULL.

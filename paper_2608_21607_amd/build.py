@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnmd.so")
 SOURCES = ["host.cpp", "ingest.cpp", "dense.hip", "dense_bf16.hip", "dense_large.hip", "dense_bf16_large.hip",
-           "dense_f16.hip", "dense_small.hip", "objective_f16.hip",
+           "dense_split.hip", "dense_small.hip", "objective_split.hip",
            "objective.hip", "sparse.hip", "solve.hip", "chol.hip", "layout.hip", "noalloc.hip"]
 ARCH = "gfx950"
 

@@ -45,15 +45,15 @@ hipError_t dense_wgs_per_cu(int rp, int* out) {
 
 hipError_t launch_dense(const float* X, int64_t rows, const float* P, int64_t blk, int rp,
                         float* Ypart, int64_t y_stride, int nsplit, float sgn,
-                        unsigned long long* gemm2_blocks, hipStream_t st) {
+                        unsigned long long* gemm2_blocks, const int* redo, hipStream_t st) {
   if (rp <= 64) return launch_dense_small(X, rows, P, blk, rp, Ypart, y_stride, nsplit, sgn, gemm2_blocks, st);
-#define CALL(R) launch_dense_t<R>(X, rows, P, blk, Ypart, y_stride, nsplit, sgn, gemm2_blocks, st)
+#define CALL(R) launch_dense_t<R>(X, rows, P, blk, Ypart, y_stride, nsplit, sgn, gemm2_blocks, redo, st)
   switch (rp) {
     case 128: return CALL(128);
     case 192: return CALL(192);
     case 256: return CALL(256);
     case 320: case 384: case 448: case 512:
-      return launch_dense_large(X, rows, P, blk, rp, Ypart, y_stride, nsplit, sgn, gemm2_blocks, st);
+      return launch_dense_large(X, rows, P, blk, rp, Ypart, y_stride, nsplit, sgn, gemm2_blocks, redo, st);
   }
 #undef CALL
   return hipErrorInvalidValue;

@@ -1,6 +1,7 @@
 // Fused dense contraction Y = sgn * max(0, X P^T) P on gfx950 fp32 MFMA (kernel templates; the
 // instantiations live in dense.hip for r_p = 128 to 256 and in dense_large.hip for larger ranks,
-// which are compiled with different register-allocation flags; r_p <= 64: dense_small.hip).
+// which are compiled with different register-allocation flags; r_p <= 64: dense_small.hip).  The
+// steps take it for the rows that dense_split.hip leaves.
 //
 // With L = X P_J^T and S-hat = max(0, L) (eq. rectify), the difference matrix of eq. updateD
 // gives Delta_{:J} P_J = sum over the nonzeros of S of (S - min(0, L)) p_j  -  S-hat P_J, and
@@ -76,6 +77,14 @@ struct DenseLaunch<128> {
 
 template <int RP>
 constexpr int dense_rows() { return 16 * DenseLaunch<RP>::MI * DenseLaunch<RP>::WAVES; }
+
+// Panel range of split s of nsplit: starts rounded down to whole 32-row blocks.
+__host__ __device__ __forceinline__ int64_t block_start(int s, int nsplit, int64_t blk) {
+  return s >= nsplit ? blk : ((int64_t)s * blk / nsplit) / 32 * 32;
+}
+
+// Rows of X per workgroup of the split kernel (dense_split.hip), r_p >= 128.
+constexpr int split_rows(int rp) { return rp > 128 ? 64 : 128; }
 
 // Direct staging of panel rows j0 .. j0+NT-1 from global memory straight into a padded LDS
 // tile; wave w fills rows w, w + WAVES, ...; a direct load writes 64 consecutive 16-byte chunks
@@ -256,11 +265,14 @@ __device__ __forceinline__ unsigned direct_step(
   return consume_tile<RP>(cur, j0, jb1, a, y, q, l16, entries);
 }
 
+// One workgroup's rows against one panel range.  redo (or NULL): an int per split and row tile of the
+// split kernel; only tiles marked there are formed.
 template <int RP>
-__global__ __launch_bounds__(64 * DenseLaunch<RP>::WAVES) void dense_kernel(
-    const float* __restrict__ X, int64_t rows, const float* __restrict__ P, int64_t blk,
-    float* __restrict__ Ypart, int64_t y_stride, int nsplit, int64_t row_tiles, float sgn,
-    unsigned long long* __restrict__ gemm2_blocks) {
+__device__ __forceinline__ void dense_rows_of(
+    float* smem, int64_t logical, const float* __restrict__ X, int64_t rows,
+    const float* __restrict__ P, int64_t blk, float* __restrict__ Ypart, int64_t y_stride,
+    int nsplit, int64_t row_tiles, float sgn, unsigned long long* __restrict__ gemm2_blocks,
+    const int* __restrict__ redo) {
   constexpr int MI = DenseLaunch<RP>::MI;
   constexpr int WAVES = DenseLaunch<RP>::WAVES;
   constexpr int CB = RP / 16;
@@ -268,19 +280,30 @@ __global__ __launch_bounds__(64 * DenseLaunch<RP>::WAVES) void dense_kernel(
   constexpr bool DIRECT = DenseLaunch<RP>::DIRECT;
   constexpr int NT = DenseLaunch<RP>::NT;
   static_assert(NT % 16 == 0 && NT % WAVES == 0, "tile shape");
-  __shared__ __attribute__((aligned(16))) float smem[(DIRECT ? 2 : 1) * NT * LS];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, l16 = lane & 15;
 
-  const int64_t logical = xcd_logical(blockIdx.x, (int64_t)gridDim.x);
   const int split = (int)(logical / row_tiles);
   const int64_t rt = logical - (int64_t)split * row_tiles;
-  const int64_t jb0 = (int64_t)split * blk / nsplit;
-  const int64_t jb1 = (int64_t)(split + 1) * blk / nsplit;
+  const int64_t jb0 = block_start(split, nsplit, blk);
+  const int64_t jb1 = block_start(split + 1, nsplit, blk);
   const int64_t row0 = rt * dense_rows<RP>() + (int64_t)wave * (16 * MI);
+  bool mine = true;  // the wave's rows are wanted
+  if (redo) {
+    constexpr int TR = split_rows(RP), PER = dense_rows<RP>() / TR;
+    static_assert(dense_rows<RP>() % TR == 0 && TR % (16 * MI) == 0, "whole tiles, whole waves");
+    const int64_t tiles = (rows + TR - 1) / TR;
+    int any = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (rt * PER + u < tiles) any |= redo[split * tiles + rt * PER + u];
+    if (!any) return;
+    __syncthreads();  // the tile before has been read
+    mine = row0 < rows && redo[split * tiles + row0 / TR] != 0;
+  }
 
   float a[MI][RP / 4];
   load_x_frags<RP, MI>(a, X, rows, row0, q, l16);
@@ -326,7 +349,7 @@ __global__ __launch_bounds__(64 * DenseLaunch<RP>::WAVES) void dense_kernel(
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int64_t row = row0 + 4 * q4 + v;
-        if (row < rows) {
+        if (mine && row < rows) {
 #pragma unroll
           for (int h = 0; h < G / 4; ++h)
             *reinterpret_cast<float4*>(&Y[row * RP + G * lane + 4 * h]) =
@@ -341,29 +364,45 @@ __global__ __launch_bounds__(64 * DenseLaunch<RP>::WAVES) void dense_kernel(
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int64_t row = row0 + 16 * mi + 4 * q + v;
-      if (row < rows) {
+      if (mine && row < rows) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) Y[row * RP + 16 * cb + l16] = sgn * y[mi][cb][v];
       }
     }
   }
-  if (gemm2_blocks && lane == 0) {
+  if (gemm2_blocks && mine && lane == 0) {
     atomicAdd(gemm2_blocks, (unsigned long long)done);
     if (entries) atomicAdd(gemm2_blocks + 1, (unsigned long long)entries);
   }
 }
 
 template <int RP>
+__global__ __launch_bounds__(64 * DenseLaunch<RP>::WAVES) void dense_kernel(
+    const float* __restrict__ X, int64_t rows, const float* __restrict__ P, int64_t blk,
+    float* __restrict__ Ypart, int64_t y_stride, int nsplit, int64_t row_tiles, float sgn,
+    unsigned long long* __restrict__ gemm2_blocks, const int* __restrict__ redo) {
+  constexpr int NT = DenseLaunch<RP>::NT;
+  __shared__ __attribute__((aligned(16))) float smem[(DenseLaunch<RP>::DIRECT ? 2 : 1) * NT * (RP + 4)];
+  // behind a split launch the workgroups take the tiles in turn (one each took 27 us to find nothing to
+  // do at 139255 rows, r_p = 256: each waits for the LDS of one before it)
+  for (int64_t wg = blockIdx.x; wg < row_tiles * nsplit; wg += gridDim.x)
+    dense_rows_of<RP>(smem, redo ? wg : xcd_logical(wg, row_tiles * nsplit), X, rows, P, blk, Ypart,
+                      y_stride, nsplit, row_tiles, sgn, gemm2_blocks, redo);
+}
+
+constexpr int64_t kRedoWgs = 512;  // of a launch behind the split kernel's
+
+template <int RP>
 static hipError_t launch_dense_t(const float* X, int64_t rows, const float* P, int64_t blk,
                                  float* Ypart, int64_t y_stride, int nsplit, float sgn,
-                                 unsigned long long* gemm2_blocks, hipStream_t st) {
+                                 unsigned long long* gemm2_blocks, const int* redo, hipStream_t st) {
   const int64_t row_tiles = (rows + dense_rows<RP>() - 1) / dense_rows<RP>();
   const int64_t total = row_tiles * nsplit;
   if (total <= 0) return hipSuccess;
   if (total > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dense_kernel<RP>), dim3((unsigned)total),
+  hipLaunchKernelGGL((dense_kernel<RP>), dim3((unsigned)(redo && total > kRedoWgs ? kRedoWgs : total)),
                      dim3(64 * DenseLaunch<RP>::WAVES), 0, st, X, rows, P, blk,
-                     Ypart, y_stride, nsplit, row_tiles, sgn, gemm2_blocks);
+                     Ypart, y_stride, nsplit, row_tiles, sgn, gemm2_blocks, redo);
   return hipGetLastError();
 }
 

@@ -19,8 +19,8 @@ hipError_t dense_wgs_per_cu_large(int rp, int* out) {
 
 hipError_t launch_dense_large(const float* X, int64_t rows, const float* P, int64_t blk, int rp,
                               float* Ypart, int64_t y_stride, int nsplit, float sgn,
-                              unsigned long long* gemm2_blocks, hipStream_t st) {
-#define CALL(R) launch_dense_t<R>(X, rows, P, blk, Ypart, y_stride, nsplit, sgn, gemm2_blocks, st)
+                              unsigned long long* gemm2_blocks, const int* redo, hipStream_t st) {
+#define CALL(R) launch_dense_t<R>(X, rows, P, blk, Ypart, y_stride, nsplit, sgn, gemm2_blocks, redo, st)
   switch (rp) {
     case 320: return CALL(320);
     case 384: return CALL(384);

@@ -94,8 +94,10 @@ struct nmd_ctx {
   std::vector<std::pair<int, bool>> enqueued;  // (step id, W-step) of the call's steps, in order
   float* Ypart = nullptr;
   float* Pbx = nullptr;  // split-bf16 panel copies (NMD_FLAG_SPLIT_BF16 at r_p = 16..512)
-  float* Pfx = nullptr;  // split-f16 panel copy (the default at r_p >= 128)
-  float* Pobj = nullptr;  // split-f16 copy of all of B for the objective, from its first use on
+  float* Psp = nullptr;  // three-term split of a step's panel (the default at r_p >= 128)
+  int* redo = nullptr;   // the tiles its contraction leaves to the fp32 kernel
+  float* Pobj = nullptr;  // three-term split of all of B for the objective, from its first use on
+  int* obj_nan = nullptr;  // whether that objective came out NaN
   int64_t ypart_floats = 0;
   float* scratch = nullptr;
   int64_t scratch_floats = 0;
@@ -116,7 +118,7 @@ struct nmd_ctx {
   int64_t dense_slots = 0;           // dense workgroups resident at once (CUs x per CU)
   int64_t dense_rows = 0;            // rows of X per dense workgroup
   bool dense_small = false;          // the r_p <= 64 split kernel
-  int f16_wgs = 0;                   // split-f16 workgroups per CU; 0: another dense kernel
+  bool dense_split = false;          // the r_p >= 128 split kernel
   hipStream_t side = nullptr;     // Gram and inverse run here, beside the contraction
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipStream_t corr = nullptr;     // the sparse correction runs here, beside the contraction
@@ -196,8 +198,10 @@ void free_device(nmd_ctx* c) {
   dfree(c->VB2);
   dfree(c->Ypart);
   dfree(c->Pbx);
-  dfree(c->Pfx);
+  dfree(c->Psp);
+  dfree(c->redo);
   dfree(c->Pobj);
+  dfree(c->obj_nan);
   dfree(c->G);
   dfree(c->Gwork);
   dfree(c->Gpart);
@@ -257,14 +261,15 @@ int64_t nsplit_for(int64_t rows, int64_t blk, int64_t rw, int64_t slots) {
   return best;
 }
 
-// The same for the split-f16 kernel, in units of a panel row of one workgroup (46 ns at r_p = 256).
+// The same for the split kernel, in units of a panel row of one workgroup (47 ns at r_p = 256).
 // Its workgroups differ in length (by the positive entries of their rows) and start behind those
 // of the side streams, so a launch ends about two workgroup lengths after an even share of the
 // work: shorter workgroups finish sooner.  Against that, a workgroup's set-up and write-back cost
-// about 40 rows, and a partial output (written here, read by the apply) 0.8 rows per row tile.
-// Measured per sweep, splits 2 / 3 / 4 / 6: 139255^2, r = 256 99.0 / 97.4 / 96.6 / 99.3 ms;
-// 34814^2, r = 200 23.0 / 21.7 / 20.9 / 20.6; 125000 x 50000, r = 512 104 / 92.8 / 89.5 / 94.6.
-int64_t nsplit_f16(int64_t rows, int64_t blk, int64_t rw, int64_t per_cu, int64_t slots) {
+// about 40 rows, and a partial output (written here, read by the apply) 0.4 rows per row tile.
+// Measured per sweep, splits 2 / 3 / 4 / 6 / 8: 139255^2, r = 256 152 / 149 / 147 / 149 / 153 ms;
+// 34814^2, r = 200, guarded 27.0 / 26.7 / 26.6 / 26.9 / 29.1; 40001 x 30011, r = 384 15.8 / 15.7 / 15.7 /
+// 16.2 / 16.9; 125000 x 50000, r = 512 140 / 134 / 130 / 126 / 132.
+int64_t nsplit_split(int64_t rows, int64_t blk, int64_t rw, int64_t slots) {
   const int64_t tiles = (rows + rw - 1) / rw;
   const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, blk / 32));
   const int64_t lo = std::min((blk + kSplitRows - 1) / kSplitRows, cap);
@@ -272,7 +277,7 @@ int64_t nsplit_f16(int64_t rows, int64_t blk, int64_t rw, int64_t per_cu, int64_
   double best_cost = 0.0;
   for (int64_t s = lo; s <= cap; ++s) {
     const double cost = ((double)(tiles * s) / (double)slots + 2.0) * ((double)blk / (double)s + 40.0) +
-                        0.8 * (double)(tiles * s) / (double)per_cu;
+                        0.4 * (double)(tiles * s);
     if (s == lo || cost < best_cost) {
       best = s;
       best_cost = cost;
@@ -307,8 +312,7 @@ int64_t nsplit_small(int64_t rows, int64_t blk, int64_t rw, int64_t rp, int64_t 
 
 int64_t nsplit(const nmd_ctx* c, int64_t rows, int64_t blk) {
   if (c->dense_small) return nsplit_small(rows, blk, c->dense_rows, c->rp, c->dense_slots);
-  if (c->f16_wgs)
-    return nsplit_f16(rows, blk, c->dense_rows, c->f16_wgs, c->dense_slots);
+  if (c->dense_split) return nsplit_split(rows, blk, c->dense_rows, c->dense_slots);
   return nsplit_for(rows, blk, c->dense_rows, c->dense_slots);
 }
 
@@ -328,16 +332,16 @@ int ensure_device(nmd_ctx* c) {
     c->device = dev;
     const int64_t rp = c->rp;
     // the split-bf16 option covers the padded ranks the bf16x3 kernels support; otherwise the
-    // split-f16 kernel takes r_p >= 128 (at 64 its first product is too short for a consumer's
-    // work: 32768 x 4096 with 9% of L positive 0.55 ms, where both products on f16 MFMA take 0.13)
+    // three-term split kernel takes r_p >= 128 (at 64 its first product is too short for a consumer's
+    // work, and half of L may be positive: both products on splits take it)
     const bool bx = (c->opt.flags & NMD_FLAG_SPLIT_BF16) && nmd::bf16x3_rank(rp);
-    const bool fx = !bx && nmd::f16_rank(rp);
-    int per_cu = nmd::f16_wgs_per_cu(rp);
-    c->f16_wgs = fx ? per_cu : 0;
-    if (!fx) HIP_TRY(c, nmd::dense_wgs_per_cu(c->rp, &per_cu));
+    const bool sp = !bx && nmd::split_rank(rp);
+    int per_cu = 1;
+    if (!sp) HIP_TRY(c, nmd::dense_wgs_per_cu(c->rp, &per_cu));
     c->dense_slots = (int64_t)prop.multiProcessorCount * std::max(per_cu, 1);
     c->dense_small = !bx && rp <= 64;
-    c->dense_rows = fx               ? nmd::f16_rows_per_wg(rp)
+    c->dense_split = sp;
+    c->dense_rows = sp               ? nmd::split_rows_per_wg(rp)
                     : c->dense_small ? nmd::dense_small_rows_per_wg()
                                      : nmd::dense_rows_per_wg(rp);
     const int64_t mpad = c->m + 256, npad = c->n + 256;
@@ -371,10 +375,13 @@ int ensure_device(nmd_ctx* c) {
     need = std::max(need, nsplit(c, c->m, c->n) * c->m);
     need = std::max(need, nsplit(c, c->n, c->m) * c->n);
     c->ypart_floats = need * rp;
+    // tiles of any step's launch: its splits x rows, each split's last tile short
+    const int64_t tiles = need / c->dense_rows + kMaxSplits;
     if (dalloc(&c->Ypart, c->ypart_floats) != hipSuccess ||
         (rp >= 320 && !bx && dalloc(&c->Ysp, std::max(c->m, c->n) * rp) != hipSuccess) ||
         (bx && dalloc(&c->Pbx, nmd::bf16x3_work_floats(std::max(c->m, c->n), rp)) != hipSuccess) ||
-        (fx && dalloc(&c->Pfx, nmd::f16_work_floats(panel, rp)) != hipSuccess)) {
+        (sp && (dalloc(&c->Psp, nmd::split_work_floats(panel, rp)) != hipSuccess ||
+                dalloc(&c->redo, tiles) != hipSuccess))) {
       free_device(c);
       return fail(c, NMD_ENOMEM, "device allocation of %lld partial-output floats failed",
                   (long long)c->ypart_floats);
@@ -433,8 +440,8 @@ int ensure_device(nmd_ctx* c) {
     }
     c->scratch_floats = std::max<int64_t>(1, std::max(c->ws.max_slots, c->hs.max_slots)) * c->rp;
     // objective partials: one per (row tile, column block, sub-split)
-    const int64_t rw = nmd::objective_f16_rank(c->rp) ? nmd::f16_rows_per_wg(c->rp)
-                                                      : nmd::dense_rows_per_wg(c->rp);
+    int64_t rw = nmd::dense_rows_per_wg(c->rp);
+    if (nmd::objective_split_rank(c->rp)) rw = std::min<int64_t>(rw, nmd::split_rows_per_wg(c->rp));
     c->objpart_count = 5 * ((c->m + rw - 1) / rw) * c->ws.nblk() * kObjSubMax + 1;
     if (dalloc(&c->scratch, c->scratch_floats) != hipSuccess ||
         dalloc(&c->objpart, c->objpart_count) != hipSuccess) {
@@ -635,15 +642,15 @@ int factor_step(nmd_ctx* c, bool wstep, int32_t block, float eta, float gamma, i
       for (int s = 0; s < (int)ns; ++s)
         jblocks += 2 * ((nmd::bf16x3_pair_start(s + 1, (int)ns, blk) -
                          nmd::bf16x3_pair_start(s, (int)ns, blk) + 31) / 32);
-    } else if (c->Pfx) {
-      HIP_TRY(c, nmd::launch_dense_f16(X, rows, PJ, blk, rp, c->Pfx, c->Ypart, y_stride, (int)ns,
-                                       -1.0f, c->g2, st));
+    } else if (c->dense_split) {
+      HIP_TRY(c, nmd::launch_dense_split(X, rows, PJ, blk, rp, c->Psp, c->Ypart, y_stride, (int)ns,
+                                         -1.0f, c->redo, c->g2, st));
       for (int s = 0; s < (int)ns; ++s)
-        jblocks += 2 * ((nmd::f16_block_start(s + 1, (int)ns, blk) -
-                         nmd::f16_block_start(s, (int)ns, blk) + 31) / 32);
+        jblocks += 2 * ((nmd::split_block_start(s + 1, (int)ns, blk) -
+                         nmd::split_block_start(s, (int)ns, blk) + 31) / 32);
     } else {
       HIP_TRY(c, nmd::launch_dense(X, rows, PJ, blk, rp, c->Ypart, y_stride, (int)ns, -1.0f,
-                                   c->g2, st));
+                                   c->g2, nullptr, st));
       for (int64_t s = 0; s < ns; ++s) jblocks += ((s + 1) * blk / ns - s * blk / ns + 15) / 16;
     }
     // slices of 16 rows x 4 panel rows examined (those entirely past the last row never run)
@@ -775,31 +782,42 @@ int check_ready(nmd_ctx* c, const void* W, const void* H) {
   return NMD_OK;
 }
 
-// Enqueues the objective kernel on the current panels A and B and its fixed-order reductions
-// into dst[0] (dst[0..4] with `metrics`).
-int enqueue_objective(nmd_ctx* c, hipStream_t st, bool metrics, double* dst) {
+// Sub-splits of a column block for an objective kernel of rw rows a workgroup, of at least `least`
+// columns each where a block has them.
+int objective_subs(const nmd_ctx* c, int64_t rw, int64_t least) {
   const Side& sd = c->ws;
-  const bool fx = nmd::objective_f16_rank(c->rp);
-  const int64_t rw = fx ? nmd::f16_rows_per_wg(c->rp) : nmd::dense_rows_per_wg(c->rp);
   const int64_t units = ((c->m + rw - 1) / rw) * sd.nblk();
   int64_t min_len = c->n;
   for (int32_t b = 0; b < sd.nblk(); ++b) min_len = std::min(min_len, sd.bounds[b + 1] - sd.bounds[b]);
-  int nsub = (int)std::min<int64_t>(kObjSubMax, std::max<int64_t>(1, (kTargetWgs + units - 1) / units));
-  nsub = (int)std::max<int64_t>(1, std::min<int64_t>(nsub, min_len / 16));
-  int64_t npart = 0;
-  if (fx) {
-    if (!c->Pobj && dalloc(&c->Pobj, nmd::f16_work_floats(c->n, c->rp)) != hipSuccess)
-      return fail(c, NMD_ENOMEM, "device allocation of the objective's panel copy failed");
-    HIP_TRY(c, nmd::launch_objective_f16(c->A, c->m, c->B, c->n, sd.d_bounds, sd.nblk(), nsub,
-                                         sd.d_rowptr, sd.d_idx, sd.d_val, c->rp, metrics, c->Pobj,
-                                         c->objpart, &npart, st));
-  } else {
-    HIP_TRY(c, nmd::launch_objective(c->A, c->m, c->B, sd.d_bounds, sd.nblk(), nsub, sd.d_rowptr,
-                                     sd.d_idx, sd.d_val, c->rp, metrics, c->objpart, &npart, st));
-  }
+  const int64_t nsub = std::min<int64_t>(kObjSubMax, std::max<int64_t>(1, (kTargetWgs + units - 1) / units));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(nsub, min_len / least));
+}
+
+// Enqueues the objective kernel on the current panels A and B and its fixed-order reductions
+// into dst[0] (dst[0..4] with `metrics`).  At r_p >= 64 on splits, and again in fp32 where that sum
+// is NaN, decided on the device.
+int enqueue_objective(nmd_ctx* c, hipStream_t st, bool metrics, double* dst) {
+  const Side& sd = c->ws;
   const int nq = metrics ? 5 : 1;
+  int64_t npart = 0;
+  const int* when = nullptr;
+  if (nmd::objective_split_rank(c->rp)) {
+    if (!c->Pobj && (dalloc(&c->Pobj, nmd::split_work_floats(c->n, c->rp)) != hipSuccess ||
+                     dalloc(&c->obj_nan, 1) != hipSuccess))
+      return fail(c, NMD_ENOMEM, "device allocation of the objective's panel copy failed");
+    const int nsub = objective_subs(c, nmd::split_rows_per_wg(c->rp), 32);
+    HIP_TRY(c, nmd::launch_objective_split(c->A, c->m, c->B, c->n, sd.d_bounds, sd.nblk(), nsub,
+                                           sd.d_rowptr, sd.d_idx, sd.d_val, c->rp, metrics, c->Pobj,
+                                           c->objpart, &npart, st));
+    if (nq * npart > c->objpart_count) return fail(c, NMD_EDEVICE, "internal: objective buffer");
+    HIP_TRY(c, nmd::launch_sum(c->objpart, npart, nq, dst, c->obj_nan, nullptr, st));
+    when = c->obj_nan;
+  }
+  const int nsub = objective_subs(c, nmd::dense_rows_per_wg(c->rp), 16);
+  HIP_TRY(c, nmd::launch_objective(c->A, c->m, c->B, sd.d_bounds, sd.nblk(), nsub, sd.d_rowptr,
+                                   sd.d_idx, sd.d_val, c->rp, metrics, c->objpart, &npart, when, st));
   if (nq * npart > c->objpart_count) return fail(c, NMD_EDEVICE, "internal: objective buffer");
-  HIP_TRY(c, nmd::launch_sum(c->objpart, npart, nq, dst, st));
+  HIP_TRY(c, nmd::launch_sum(c->objpart, npart, nq, dst, nullptr, when, st));
   return NMD_OK;
 }
 
@@ -1244,7 +1262,7 @@ int nmd_rectified_contraction(const float* A, int64_t rows, const float* B, int6
     return fail(nullptr, NMD_EINVAL,
                 "r = %d unsupported: use 16, 32, 48, 64 or a multiple of 64 up to 512", r);
   hipError_t e =
-      nmd::launch_dense(A, rows, B, blk, r, Y, 0, 1, 1.0f, nullptr, (hipStream_t)hip_stream);
+      nmd::launch_dense(A, rows, B, blk, r, Y, 0, 1, 1.0f, nullptr, nullptr, (hipStream_t)hip_stream);
   if (e != hipSuccess) return fail(nullptr, NMD_EDEVICE, "launch failed: %s", hipGetErrorString(e));
   return NMD_OK;
 }

@@ -121,8 +121,10 @@ __global__ void guard_kernel(const double* __restrict__ q_old, const double* __r
 
 // Workgroup k: sum k of gridDim.x, per-thread strided partial sums, then a fixed-order tree.
 __global__ __launch_bounds__(1024) void sum_kernel(const double* __restrict__ partial,
-                                                   int64_t count, double* __restrict__ out) {
+                                                   int64_t count, double* __restrict__ out,
+                                                   int* is_nan, const int* when) {
   __shared__ double red[1024];
+  if (when && *when == 0) return;
   const double* p = partial + (int64_t)blockIdx.x * count;
   double s = 0.0;
   for (int64_t e = threadIdx.x; e < count; e += 1024) s += p[e];
@@ -132,7 +134,10 @@ __global__ __launch_bounds__(1024) void sum_kernel(const double* __restrict__ pa
     if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = red[0];
+    if (is_nan && blockIdx.x == 0) *is_nan = isnan(red[0]);
+  }
 }
 
 static inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -207,8 +212,10 @@ hipError_t launch_guard(const double* q_old, const double* q_new, double tol2, i
   return hipGetLastError();
 }
 
-hipError_t launch_sum(const double* partial, int64_t count, int n, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sum_kernel, dim3((unsigned)n), dim3(1024), 0, st, partial, count, out);
+hipError_t launch_sum(const double* partial, int64_t count, int n, double* out, int* is_nan,
+                      const int* when, hipStream_t st) {
+  hipLaunchKernelGGL(sum_kernel, dim3((unsigned)n), dim3(1024), 0, st, partial, count, out, is_nan,
+                     when);
   return hipGetLastError();
 }
 

@@ -48,15 +48,16 @@ hipError_t dense_wgs_per_cu(int rp, int* out);
 hipError_t dense_wgs_per_cu_large(int rp, int* out);
 hipError_t launch_dense_large(const float* X, int64_t rows, const float* P, int64_t blk, int rp,
                               float* Ypart, int64_t y_stride, int nsplit, float sgn,
-                              unsigned long long* gemm2_blocks, hipStream_t st);
+                              unsigned long long* gemm2_blocks, const int* redo, hipStream_t st);
 
 // Y_s = sgn * max(0, X P^T) P over the split s of the rows of P (rows of X: `rows`).  Ypart
 // holds nsplit buffers of y_stride floats each (row-major rows x rp).  When gemm2_blocks is not
 // NULL it receives (atomically) the number of slices (16 rows x 4 panel rows) that ran the
-// second contraction; the others had no positive L entry and were skipped.
+// second contraction; the others had no positive L entry and were skipped.  redo (rp >= 128, or
+// NULL for all rows): only the tiles launch_dense_split marked there.
 hipError_t launch_dense(const float* X, int64_t rows, const float* P, int64_t blk, int rp,
                         float* Ypart, int64_t y_stride, int nsplit, float sgn,
-                        unsigned long long* gemm2_blocks, hipStream_t st);
+                        unsigned long long* gemm2_blocks, const int* redo, hipStream_t st);
 
 // Both products on split bf16 MFMA (dense_bf16.h), rp in {16, 32, 64, 128, 256, 512}
 // (bf16x3_rank): splits the blk x rp
@@ -85,20 +86,21 @@ hipError_t launch_dense_small(const float* X, int64_t rows, const float* P, int6
                               float* Ypart, int64_t y_stride, int nsplit, float sgn,
                               unsigned long long* counts, hipStream_t st);
 
-// The same product (as launch_dense) with its first product on f16 MFMA of two-term splits at
-// fp32 accuracy (split_f16.h), for f16_rank(rp): `work` holds f16_work_floats(blk, rp) floats, the
-// panel range of split s starts at f16_block_start(s, nsplit, blk) (whole 32-row blocks), and
-// counts[1] receives the positive entries of max(0, L).
-bool f16_rank(int rp);
-int64_t f16_work_floats(int64_t blk, int rp);
-// Splits a panel (blk rows) into `work`.
-hipError_t launch_split_f16(const float* P, int64_t blk, int rp, float* work, hipStream_t st);
-int f16_rows_per_wg(int rp);
-int f16_wgs_per_cu(int rp);
-int64_t f16_block_start(int s, int nsplit, int64_t blk);
-hipError_t launch_dense_f16(const float* X, int64_t rows, const float* P, int64_t blk, int rp,
-                            float* work, float* Ypart, int64_t y_stride, int nsplit, float sgn,
-                            unsigned long long* counts, hipStream_t st);
+// The same product (as launch_dense) with its first product on bf16 MFMA of three-term splits
+// (split_wide.h), for split_rank(rp): `work` holds split_work_floats(blk, rp) floats, `redo` an int
+// per split and split_rows_per_wg(rp) rows, the panel range of split s starts at
+// split_block_start(s, nsplit, blk) (whole 32-row blocks), and counts[1] receives the positive
+// entries of max(0, L).  Rows where L is dense, and those whose values the splits cannot hold, are
+// formed by launch_dense behind it.
+bool split_rank(int rp);
+int64_t split_work_floats(int64_t blk, int rp);
+// Splits a panel (blk rows) into `work` (rp a multiple of 64).
+hipError_t launch_panel_split(const float* P, int64_t blk, int rp, float* work, hipStream_t st);
+int split_rows_per_wg(int rp);
+int64_t split_block_start(int s, int nsplit, int64_t blk);
+hipError_t launch_dense_split(const float* X, int64_t rows, const float* P, int64_t blk, int rp,
+                              float* work, float* Ypart, int64_t y_stride, int nsplit, float sgn,
+                              int* redo, unsigned long long* counts, hipStream_t st);
 
 // Sparse correction: for every item, c = sum over its entries of (s - min(0, x_row . p_j)) p_j;
 // a row with a single item gets Y[row] = c (accumulate = 0) or Y[row] += c (accumulate = 1);
@@ -183,21 +185,24 @@ hipError_t launch_guard(const double* q_old, const double* q_new, double tol2, i
 // Objective: per-workgroup fp64 sums of the eq. SLloss terms over (row tile, column block,
 // sub-split); rowptr holds, per column block, the row pointers of the W-side entries.  With
 // `metrics`, five sums (objective and reconstruction measures) laid out as
-// partial[k * npartial + workgroup], k = 0..4; otherwise one.
+// partial[k * npartial + workgroup], k = 0..4; otherwise one.  `when` (or NULL): only where it
+// points at something not zero.
 hipError_t launch_objective(const float* X, int64_t rows, const float* P, const int64_t* cbounds,
                             int nblk, int nsub, const int64_t* rowptr, const int32_t* idx,
                             const float* val, int rp, bool metrics, double* partial,
-                            int64_t* npartial, hipStream_t st);
-// The same with L on f16 MFMA of two-term splits (split_f16.h), for objective_f16_rank(rp): P is
-// the panel of all n columns, `work` holds f16_work_floats(n, rp) floats.
-bool objective_f16_rank(int rp);
-hipError_t launch_objective_f16(const float* X, int64_t rows, const float* P, int64_t n,
-                                const int64_t* cbounds, int nblk, int nsub, const int64_t* rowptr,
-                                const int32_t* idx, const float* val, int rp, bool metrics,
-                                float* work, double* partial, int64_t* npartial, hipStream_t st);
+                            int64_t* npartial, const int* when, hipStream_t st);
+// The same with L on bf16 MFMA of three-term splits (split_wide.h), for objective_split_rank(rp):
+// P is the panel of all n columns, `work` holds split_work_floats(n, rp) floats.  A sum is NaN
+// where a value lies outside the splits' range.
+bool objective_split_rank(int rp);
+hipError_t launch_objective_split(const float* X, int64_t rows, const float* P, int64_t n,
+                                  const int64_t* cbounds, int nblk, int nsub, const int64_t* rowptr,
+                                  const int32_t* idx, const float* val, int rp, bool metrics,
+                                  float* work, double* partial, int64_t* npartial, hipStream_t st);
 // out[k] = sum of partial[k * count .. + count), k < n, in a fixed order (out: device memory, or
-// pinned host memory).
-hipError_t launch_sum(const double* partial, int64_t count, int n, double* out, hipStream_t st);
+// pinned host memory); *is_nan (or NULL) = whether sum 0 is NaN.  `when` as above.
+hipError_t launch_sum(const double* partial, int64_t count, int n, double* out, int* is_nan,
+                      const int* when, hipStream_t st);
 
 // The message nmd_last_error(NULL) returns for the entry points without a context: sets it and
 // returns `code`, or clears it.

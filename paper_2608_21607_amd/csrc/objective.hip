@@ -196,13 +196,15 @@ __device__ __forceinline__ void objective_tile(ObjState<DenseLaunch<RP>::MI>& st
 }
 
 // Per workgroup: partial[k * gridDim.x + workgroup] = its share of sum k (k = 0 only, or 0..4
-// in the metrics variant).  Same launch shapes and panel pipeline as the dense contraction.
+// in the metrics variant).  Same launch shapes and panel pipeline as the dense contraction.  `when`
+// (or NULL): nothing is done where it points at zero.
 template <int RP, bool METRICS>
 __global__ __launch_bounds__(64 * DenseLaunch<RP>::WAVES) void objective_kernel(
     const float* __restrict__ X, int64_t rows, const float* __restrict__ P,
     const int64_t* __restrict__ cbounds, int nsub, const int64_t* __restrict__ rowptr,
     const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t row_tiles,
-    double* __restrict__ partial) {
+    double* __restrict__ partial, const int* when) {
+  if (when && *when == 0) return;
   constexpr int MI = DenseLaunch<RP>::MI;
   constexpr int WAVES = DenseLaunch<RP>::WAVES;
   constexpr int NT = DenseLaunch<RP>::NT;
@@ -279,7 +281,7 @@ static hipError_t launch_objective_t(const float* X, int64_t rows, const float* 
                                      const int64_t* cbounds, int nblk, int nsub,
                                      const int64_t* rowptr, const int32_t* idx, const float* val,
                                      bool metrics, double* partial, int64_t* npartial,
-                                     hipStream_t st) {
+                                     const int* when, hipStream_t st) {
   const int64_t row_tiles = (rows + dense_rows<RP>() - 1) / dense_rows<RP>();
   const int64_t total = row_tiles * nblk * nsub;
   *npartial = total;
@@ -288,24 +290,32 @@ static hipError_t launch_objective_t(const float* X, int64_t rows, const float* 
   const dim3 block(64 * DenseLaunch<RP>::WAVES);
   if (metrics)
     hipLaunchKernelGGL((objective_kernel<RP, true>), dim3((unsigned)total), block, 0, st, X,
-                       rows, P, cbounds, nsub, rowptr, idx, val, row_tiles, partial);
+                       rows, P, cbounds, nsub, rowptr, idx, val, row_tiles, partial, when);
   else
     hipLaunchKernelGGL((objective_kernel<RP, false>), dim3((unsigned)total), block, 0, st, X,
-                       rows, P, cbounds, nsub, rowptr, idx, val, row_tiles, partial);
+                       rows, P, cbounds, nsub, rowptr, idx, val, row_tiles, partial, when);
   return hipGetLastError();
 }
 
 hipError_t launch_objective(const float* X, int64_t rows, const float* P, const int64_t* cbounds,
                             int nblk, int nsub, const int64_t* rowptr, const int32_t* idx,
                             const float* val, int rp, bool metrics, double* partial,
-                            int64_t* npartial, hipStream_t st) {
+                            int64_t* npartial, const int* when, hipStream_t st) {
 #define CALL(R)                                                                                \
   launch_objective_t<R>(X, rows, P, cbounds, nblk, nsub, rowptr, idx, val, metrics, partial, \
-                        npartial, st)
-  switch (rp) {  // r_p >= 64: objective_f16.hip
+                        npartial, when, st)
+  switch (rp) {
     case 16: return CALL(16);
     case 32: return CALL(32);
     case 48: return CALL(48);
+    case 64: return CALL(64);
+    case 128: return CALL(128);
+    case 192: return CALL(192);
+    case 256: return CALL(256);
+    case 320: return CALL(320);
+    case 384: return CALL(384);
+    case 448: return CALL(448);
+    case 512: return CALL(512);
   }
 #undef CALL
   return hipErrorInvalidValue;

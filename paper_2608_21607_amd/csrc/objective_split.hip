@@ -1,26 +1,27 @@
-// The objective and the reconstruction measures (sums q0 .. q4 of objective.hip) with L on f16
-// MFMA at fp32 accuracy (split_f16.h), for r_p a multiple of 64.
+// The objective and the reconstruction measures (sums q0 .. q4 of objective.hip) with L on bf16
+// MFMA of three-term splits (split_wide.h), for r_p a multiple of 64.
 //
 // The producers are the contraction's; a consumer takes the terms of its 32 x 32 tiles of L from
 // LDS, one block behind them.  Each lane owns one row and four of every eight columns (at r_p >
-// 256, where two consumers share a tile, of every other sixteen), and walks the row's nonzeros in
+// 128, where two consumers share a tile, of every other sixteen), and walks the row's nonzeros in
 // step with the blocks: the walk keeps two entries ahead in registers, so that taking one does not
 // wait for the next.  Every term is taken once from one L, as in objective.hip: an entry takes
 // its own terms and zeroes its L before the branch-free pass that adds max(0, L)^2 for the others.
 //
-// What bounds it: at r_p >= 192 the f16 matrix rate, as the contraction without entries; below, the
-// consumers' vector work (two workgroups per CU share it).  139255 x 139255, r = 256 with 0.09%
-// nonzeros: 82 -> 30 ms a call; 60000 x 30000, r = 512 17.4 -> 6.3; 30000^2, r = 320 6.9 -> 2.4,
-// r = 128 2.8 -> 1.2, r = 64 1.9 -> 1.0.  The rms error of L against fp64 is about half the fp32
-// MFMA's; its mean error is -6e-9 of L (the f16 unit truncates below its sums' last place) where
-// the fp32 unit's is 1e-10, so a sum over all entries is within about 2e-8.
+// What bounds it: the bf16 matrix rate, as the contraction without entries.  139255 x 139255, r = 256
+// with 0.09% nonzeros: 82 -> 53 ms a call (fp32 MFMA before); the sums agree with the fp32 kernel's to
+// its rounding, and their mean error is zero (two-term f16 splits, which drop the product of the low
+// halves: -6e-9 of L).
+//
+// A workgroup that met a value outside the splits' range reports NaN, and objective.hip's kernel runs
+// behind this one where the sum is NaN.
 
 #include <climits>
 
-#include "split_f16.h"
+#include "split_wide.h"
 
 namespace nmd {
-namespace fx {
+namespace sw {
 
 struct Walk {
   int64_t ptr, end;
@@ -43,9 +44,8 @@ __device__ __forceinline__ void walk_next(Walk& w, const int32_t* __restrict__ i
 // q[0] is q0 (or, without METRICS, q0 + q1), q[1] .. q[4] as in objective.hip.
 template <int RP, bool METRICS>
 __device__ __forceinline__ void tile_terms(double (&q)[5], Walk& w, const float* zt, int j0, int lo,
-                                           int hi, int zexp,
-                                           const int4 (&pe)[4 / Cfg<RP>::KS], int rg, int cp,
-                                           int lane, const int32_t* __restrict__ idx,
+                                           int hi, int rg, int cp, int lane,
+                                           const int32_t* __restrict__ idx,
                                            const float* __restrict__ val) {
   using C = Cfg<RP>;
   constexpr int NU = 4 / C::KS;  // groups of four registers this consumer takes
@@ -60,10 +60,7 @@ __device__ __forceinline__ void tile_terms(double (&q)[5], Walk& w, const float*
       const float4 b = *reinterpret_cast<const float4*>(src + C::ZT + 256 * u);
       a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
     }
-    z[4 * u] = ldexpf(a.x, zexp - pe[u].x);
-    z[4 * u + 1] = ldexpf(a.y, zexp - pe[u].y);
-    z[4 * u + 2] = ldexpf(a.z, zexp - pe[u].z);
-    z[4 * u + 3] = ldexpf(a.w, zexp - pe[u].w);
+    z[4 * u] = a.x; z[4 * u + 1] = a.y; z[4 * u + 2] = a.z; z[4 * u + 3] = a.w;
   }
   if (j0 < lo || j0 + 32 > hi) {  // columns of the neighbouring ranges
 #pragma unroll
@@ -116,16 +113,19 @@ __device__ __forceinline__ void tile_terms(double (&q)[5], Walk& w, const float*
 
 // Workgroups over (row tile, column block, sub-split); partial[k * gridDim.x + workgroup] = its
 // share of sum k.  The split panel covers all n columns in 32-column blocks from 0; a unit takes
-// the blocks its columns touch and masks the others' columns.
+// the blocks its columns touch and masks the others' columns.  Sub-splits start at whole blocks, so
+// only the ends of a column block are taken twice (cut anywhere, sixteen ranges of 256 columns took
+// three times the blocks).
 template <int RP, bool METRICS>
-__global__ __launch_bounds__(512, 2 * Cfg<RP>::WGS) void objective_f16_kernel(
+__global__ __launch_bounds__(512, 2 * Cfg<RP>::WGS) void objective_split_kernel(
     const float* __restrict__ X, int64_t rows, const float* __restrict__ split,
-    const int* __restrict__ exps, const int64_t* __restrict__ cbounds, int nsub,
+    const int* __restrict__ bad_blocks, const int64_t* __restrict__ cbounds, int nsub,
     const int64_t* __restrict__ rowptr, const int32_t* __restrict__ idx,
     const float* __restrict__ val, int64_t row_tiles, double* __restrict__ partial) {
   using C = Cfg<RP>;
   constexpr int NQ = METRICS ? 5 : 1;
   __shared__ __attribute__((aligned(16))) float smem[C::LDS];
+  __shared__ int bad;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -135,22 +135,26 @@ __global__ __launch_bounds__(512, 2 * Cfg<RP>::WGS) void objective_f16_kernel(
   const int64_t rt = logical - unit * row_tiles;
   const int b = (int)(unit / nsub), s = (int)(unit - (int64_t)b * nsub);
   const int64_t cb = cbounds[b], len = cbounds[b + 1] - cb;
-  const int lo = (int)(cb + (int64_t)s * len / nsub);  // columns < 2^31
-  const int hi = (int)(cb + (int64_t)(s + 1) * len / nsub);
+  auto cut = [&](int k) {
+    if (k == 0 || k == nsub) return cb + (k ? len : 0);
+    const int64_t c = (cb + k * len / nsub) / 32 * 32;
+    return c > cb ? c : cb;
+  };
+  const int lo = (int)cut(s), hi = (int)cut(s + 1);  // columns < 2^31
   const int64_t row0 = rt * C::ROWS;
   const int a0 = lo & ~31;
   const int64_t nb = lo < hi ? ((int64_t)hi - a0 + 31) / 32 : 0;
-  float* const zbuf = smem + C::NBUF * C::BLK;
-  float* const ldsx = zbuf + 4 * C::ZT;
+  float* const zbuf = smem + 2 * C::SLICE;
 
   double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   if (wave < 4) {
-    u32x4 xh[C::KC], xl[C::KC];
-    load_x<RP>(xh, xl, X, rows, row0, wave, lane >> 5, lane & 31, ldsx);
-    wg_barrier();
-    produce<RP>(smem, split + (int64_t)a0 * RP, nb, xh, xl, wave, lane);
+    u32x4 xh[C::KC], xm[C::KC], xl[C::KC];
+    const bool in = load_x<RP>(xh, xm, xl, X, rows, row0, wave, lane >> 5, lane & 31);
+    produce<RP>(smem, split + (int64_t)a0 / 32 * (48 * RP), nb, -1, nullptr, xh, xm, xl, wave, lane);
+    if (!in) bad = 1;
   } else {
     __builtin_amdgcn_s_setprio(3);
+    if (tid == 256) bad = 0;
     const int cw = wave - 4, rg = cw / C::KS, cp = cw % C::KS;
     const int64_t row = row0 + 32 * rg + (lane & 31);
     Walk w{0, 0, INT_MAX, INT_MAX, 0.f, 0.f};
@@ -172,31 +176,17 @@ __global__ __launch_bounds__(512, 2 * Cfg<RP>::WGS) void objective_f16_kernel(
         w.v1 = val[l + 1];
       }
     }
-    if constexpr (C::KS == 2) wg_barrier();  // the producers' row maxima
-    wg_barrier();                            // the row exponents
-    const int zexp = -reinterpret_cast<const int*>(ldsx + 128)[32 * rg + (lane & 31)];
-    // the scale exponents of the lane's columns, read a block ahead
-    constexpr int NU = 4 / C::KS;
-    const int* ep = exps + a0 + 8 * NU * cp + 4 * (lane >> 5);
-    int4 en[NU];
-    if (nb > 0) {
-#pragma unroll
-      for (int u = 0; u < NU; ++u) en[u] = *reinterpret_cast<const int4*>(ep + 8 * u);
-    }
-    consumer_barrier();
+    int out = 0;
+    for (int64_t k = lane; k < nb; k += 64) out |= bad_blocks[a0 / 32 + k];
+    s3::lds_barrier();
     for (int64_t k = 0; k < nb; ++k) {
-      consumer_barrier();  // the tiles of block k are in LDS
-      int4 pe[NU];
-#pragma unroll
-      for (int u = 0; u < NU; ++u) pe[u] = en[u];
-      ep += 32;
-      if (k + 1 < nb) {
-#pragma unroll
-        for (int u = 0; u < NU; ++u) en[u] = *reinterpret_cast<const int4*>(ep + 8 * u);
-      }
-      tile_terms<RP, METRICS>(q, w, zbuf + (int)(k & 1) * (4 * C::ZT), a0 + 32 * (int)k, lo, hi,
-                              zexp, pe, rg, cp, lane, idx, val);
+      s3::lds_barrier();
+      if constexpr (C::SL == 2) s3::lds_barrier();
+      // the tiles of block k are in LDS
+      tile_terms<RP, METRICS>(q, w, zbuf + (int)(k & 1) * (4 * C::ZT), a0 + 32 * (int)k, lo, hi, rg,
+                              cp, lane, idx, val);
     }
+    if (out) bad = 1;
   }
   // the consumers' sums, in a fixed order; the panel blocks' LDS is free
   double* red = reinterpret_cast<double*>(smem);
@@ -211,11 +201,12 @@ __global__ __launch_bounds__(512, 2 * Cfg<RP>::WGS) void objective_f16_kernel(
   wg_barrier();
   if (tid < NQ)
     partial[(int64_t)tid * gridDim.x + logical] =
-        (red[4 * tid] + red[4 * tid + 1]) + (red[4 * tid + 2] + red[4 * tid + 3]);
+        bad ? __builtin_nan("")
+            : (red[4 * tid] + red[4 * tid + 1]) + (red[4 * tid + 2] + red[4 * tid + 3]);
 }
 
 template <int RP>
-static hipError_t objective_t(const float* X, int64_t rows, const float* split, const int* exps,
+static hipError_t objective_t(const float* X, int64_t rows, const float* work, int64_t n,
                               const int64_t* cbounds, int nblk, int nsub, const int64_t* rowptr,
                               const int32_t* idx, const float* val, bool metrics, double* partial,
                               int64_t* npartial, hipStream_t st) {
@@ -225,28 +216,28 @@ static hipError_t objective_t(const float* X, int64_t rows, const float* split, 
   *npartial = total;
   if (total <= 0) return hipSuccess;
   if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+  const int* bad = reinterpret_cast<const int*>(work + blocks_of(n) * (48 * (int64_t)RP));
   if (metrics)
-    hipLaunchKernelGGL((objective_f16_kernel<RP, true>), dim3((unsigned)total), dim3(512), 0, st, X,
-                       rows, split, exps, cbounds, nsub, rowptr, idx, val, row_tiles, partial);
+    hipLaunchKernelGGL((objective_split_kernel<RP, true>), dim3((unsigned)total), dim3(512), 0, st, X,
+                       rows, work, bad, cbounds, nsub, rowptr, idx, val, row_tiles, partial);
   else
-    hipLaunchKernelGGL((objective_f16_kernel<RP, false>), dim3((unsigned)total), dim3(512), 0, st, X,
-                       rows, split, exps, cbounds, nsub, rowptr, idx, val, row_tiles, partial);
+    hipLaunchKernelGGL((objective_split_kernel<RP, false>), dim3((unsigned)total), dim3(512), 0, st, X,
+                       rows, work, bad, cbounds, nsub, rowptr, idx, val, row_tiles, partial);
   return hipGetLastError();
 }
 
-}  // namespace fx
+}  // namespace sw
 
-bool objective_f16_rank(int rp) { return rp >= 64 && rp <= 512 && rp % 64 == 0; }
+bool objective_split_rank(int rp) { return rp >= 64 && rp <= 512 && rp % 64 == 0; }
 
-hipError_t launch_objective_f16(const float* X, int64_t rows, const float* P, int64_t n,
-                                const int64_t* cbounds, int nblk, int nsub, const int64_t* rowptr,
-                                const int32_t* idx, const float* val, int rp, bool metrics,
-                                float* work, double* partial, int64_t* npartial, hipStream_t st) {
-  hipError_t e = launch_split_f16(P, n, rp, work, st);
+hipError_t launch_objective_split(const float* X, int64_t rows, const float* P, int64_t n,
+                                  const int64_t* cbounds, int nblk, int nsub, const int64_t* rowptr,
+                                  const int32_t* idx, const float* val, int rp, bool metrics,
+                                  float* work, double* partial, int64_t* npartial, hipStream_t st) {
+  hipError_t e = launch_panel_split(P, n, rp, work, st);
   if (e != hipSuccess) return e;
-  const int* exps = reinterpret_cast<const int*>(work + fx::padded_rows(n) * rp);
-#define CALL(R)                                                                                \
-  fx::objective_t<R>(X, rows, work, exps, cbounds, nblk, nsub, rowptr, idx, val, metrics, partial, \
+#define CALL(R)                                                                                  \
+  sw::objective_t<R>(X, rows, work, n, cbounds, nblk, nsub, rowptr, idx, val, metrics, partial, \
                      npartial, st)
   switch (rp) {
     case 64: return CALL(64);

@@ -61,6 +61,9 @@ struct Range {
     most = t > most ? t : most;
     least = t - 1u < least ? t - 1u : least;  // zero wraps past every other
   }
+  // Keeps the compiler from putting the comparisons off to where the answer is used (and their
+  // operands in registers until then).
+  __device__ __forceinline__ void settle() { asm volatile("" : "+v"(most), "+v"(least)); }
   __device__ __forceinline__ bool outside() const {
     return most >= 0x7f000000u || least < 0x09800000u - 1u;
   }
