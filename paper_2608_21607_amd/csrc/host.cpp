@@ -336,8 +336,10 @@ int ensure_device(nmd_ctx* c) {
     // work, and half of L may be positive: both products on splits take it)
     const bool bx = (c->opt.flags & NMD_FLAG_SPLIT_BF16) && nmd::bf16x3_rank(rp);
     const bool sp = !bx && nmd::split_rank(rp);
+    // a CU holds one workgroup of the split and of the bf16x3 kernels (their LDS); 60000 x 50000, r =
+    // 10 with the option 2.89 ms a sweep, 2.96 with its ranges cut for four, r = 64 5.30 and 5.33
     int per_cu = 1;
-    if (!sp) HIP_TRY(c, nmd::dense_wgs_per_cu(c->rp, &per_cu));
+    if (!sp && !bx) HIP_TRY(c, nmd::dense_wgs_per_cu(c->rp, &per_cu));
     c->dense_slots = (int64_t)prop.multiProcessorCount * std::max(per_cu, 1);
     c->dense_small = !bx && rp <= 64;
     c->dense_split = sp;
