@@ -320,6 +320,32 @@ int gram_chunks(int64_t blk) {
   return (int)std::min<int64_t>(64, std::max<int64_t>(1, blk / 256));
 }
 
+// The buffers of the dense kernel in use; false if one does not fit.
+bool alloc_outputs(nmd_ctx* c) {
+  // Partial outputs: the largest (splits x rows) over W-steps, H-steps and full half-sweeps.
+  int64_t need = 0;
+  // panel rows of the longest step
+  int64_t panel = c->opt.mode == NMD_STOCHASTIC ? 1 : std::max(c->m, c->n);
+  for (size_t k = 0; k + 1 < c->cb.size(); ++k) {
+    const int64_t blk = c->cb[k + 1] - c->cb[k];
+    panel = std::max(panel, blk);
+    need = std::max(need, nsplit(c, c->m, blk) * c->m);
+  }
+  for (size_t k = 0; k + 1 < c->rb.size(); ++k) {
+    const int64_t blk = c->rb[k + 1] - c->rb[k];
+    panel = std::max(panel, blk);
+    need = std::max(need, nsplit(c, c->n, blk) * c->n);
+  }
+  need = std::max(need, nsplit(c, c->m, c->n) * c->m);
+  need = std::max(need, nsplit(c, c->n, c->m) * c->n);
+  c->ypart_floats = need * c->rp;
+  if (dalloc(&c->Ypart, c->ypart_floats) != hipSuccess) return false;
+  if (!c->dense_split) return true;
+  // tiles of any step's launch: its splits x rows, each split's last tile short
+  return dalloc(&c->Psp, nmd::split_work_floats(panel, c->rp)) == hipSuccess &&
+         dalloc(&c->redo, need / c->dense_rows + kMaxSplits) == hipSuccess;
+}
+
 int ensure_device(nmd_ctx* c) {
   if (!c->dev_ready) {
     int dev = 0;
@@ -335,17 +361,19 @@ int ensure_device(nmd_ctx* c) {
     // three-term split kernel takes r_p >= 128 (at 64 its first product is too short for a consumer's
     // work, and half of L may be positive: both products on splits take it)
     const bool bx = (c->opt.flags & NMD_FLAG_SPLIT_BF16) && nmd::bf16x3_rank(rp);
-    const bool sp = !bx && nmd::split_rank(rp);
     // a CU holds one workgroup of the split and of the bf16x3 kernels (their LDS); 60000 x 50000, r =
     // 10 with the option 2.89 ms a sweep, 2.96 with its ranges cut for four, r = 64 5.30 and 5.33
     int per_cu = 1;
-    if (!sp && !bx) HIP_TRY(c, nmd::dense_wgs_per_cu(c->rp, &per_cu));
-    c->dense_slots = (int64_t)prop.multiProcessorCount * std::max(per_cu, 1);
+    if (!bx) HIP_TRY(c, nmd::dense_wgs_per_cu(c->rp, &per_cu));
     c->dense_small = !bx && rp <= 64;
-    c->dense_split = sp;
-    c->dense_rows = sp               ? nmd::split_rows_per_wg(rp)
-                    : c->dense_small ? nmd::dense_small_rows_per_wg()
-                                     : nmd::dense_rows_per_wg(rp);
+    auto choose = [&](bool split) {
+      c->dense_split = split;
+      c->dense_slots = (int64_t)prop.multiProcessorCount * (split ? 1 : std::max(per_cu, 1));
+      c->dense_rows = split            ? nmd::split_rows_per_wg(rp)
+                      : c->dense_small ? nmd::dense_small_rows_per_wg()
+                                       : nmd::dense_rows_per_wg(rp);
+    };
+    choose(!bx && nmd::split_rank(rp));
     const int64_t mpad = c->m + 256, npad = c->n + 256;
     if (dalloc(&c->A, mpad * rp) != hipSuccess || dalloc(&c->B, npad * rp) != hipSuccess ||
         dalloc(&c->VA, mpad * rp) != hipSuccess || dalloc(&c->VB, npad * rp) != hipSuccess ||
@@ -360,33 +388,22 @@ int ensure_device(nmd_ctx* c) {
       free_device(c);
       return fail(c, NMD_ENOMEM, "device allocation of the factor workspaces failed");
     }
-    // Partial outputs: the largest (splits x rows) over W-steps, H-steps and full half-sweeps.
-    int64_t need = 0;
-    // panel rows of the longest step
-    int64_t panel = c->opt.mode == NMD_STOCHASTIC ? 1 : std::max(c->m, c->n);
-    for (size_t k = 0; k + 1 < c->cb.size(); ++k) {
-      const int64_t blk = c->cb[k + 1] - c->cb[k];
-      panel = std::max(panel, blk);
-      need = std::max(need, nsplit(c, c->m, blk) * c->m);
-    }
-    for (size_t k = 0; k + 1 < c->rb.size(); ++k) {
-      const int64_t blk = c->rb[k + 1] - c->rb[k];
-      panel = std::max(panel, blk);
-      need = std::max(need, nsplit(c, c->n, blk) * c->n);
-    }
-    need = std::max(need, nsplit(c, c->m, c->n) * c->m);
-    need = std::max(need, nsplit(c, c->n, c->m) * c->n);
-    c->ypart_floats = need * rp;
-    // tiles of any step's launch: its splits x rows, each split's last tile short
-    const int64_t tiles = need / c->dense_rows + kMaxSplits;
-    if (dalloc(&c->Ypart, c->ypart_floats) != hipSuccess ||
-        (rp >= 320 && !bx && dalloc(&c->Ysp, std::max(c->m, c->n) * rp) != hipSuccess) ||
-        (bx && dalloc(&c->Pbx, nmd::bf16x3_work_floats(std::max(c->m, c->n), rp)) != hipSuccess) ||
-        (sp && (dalloc(&c->Psp, nmd::split_work_floats(panel, rp)) != hipSuccess ||
-                dalloc(&c->redo, tiles) != hipSuccess))) {
+    if ((rp >= 320 && !bx && dalloc(&c->Ysp, std::max(c->m, c->n) * rp) != hipSuccess) ||
+        (bx && dalloc(&c->Pbx, nmd::bf16x3_work_floats(std::max(c->m, c->n), rp)) != hipSuccess)) {
       free_device(c);
-      return fail(c, NMD_ENOMEM, "device allocation of %lld partial-output floats failed",
-                  (long long)c->ypart_floats);
+      return fail(c, NMD_ENOMEM, "device allocation of the factor workspaces failed");
+    }
+    while (!alloc_outputs(c)) {
+      (void)hipGetLastError();
+      dfree(c->Ypart);
+      dfree(c->Psp);
+      dfree(c->redo);
+      if (!c->dense_split) {
+        free_device(c);
+        return fail(c, NMD_ENOMEM, "device allocation of %lld partial-output floats failed",
+                    (long long)c->ypart_floats);
+      }
+      choose(false);  // the fp32 kernel needs no copy of the panel
     }
     if (hipHostMalloc((void**)&c->h_status, 2 * sizeof(int)) != hipSuccess ||
         hipHostMalloc((void**)&c->h_obj, 8 * sizeof(double)) != hipSuccess) {
@@ -797,16 +814,19 @@ int objective_subs(const nmd_ctx* c, int64_t rw, int64_t least) {
 
 // Enqueues the objective kernel on the current panels A and B and its fixed-order reductions
 // into dst[0] (dst[0..4] with `metrics`).  At r_p >= 64 on splits, and again in fp32 where that sum
-// is NaN, decided on the device.
+// is NaN, decided on the device; in fp32 alone where the split panel does not fit the memory left.
 int enqueue_objective(nmd_ctx* c, hipStream_t st, bool metrics, double* dst) {
   const Side& sd = c->ws;
   const int nq = metrics ? 5 : 1;
   int64_t npart = 0;
   const int* when = nullptr;
-  if (nmd::objective_split_rank(c->rp)) {
-    if (!c->Pobj && (dalloc(&c->Pobj, nmd::split_work_floats(c->n, c->rp)) != hipSuccess ||
-                     dalloc(&c->obj_nan, 1) != hipSuccess))
-      return fail(c, NMD_ENOMEM, "device allocation of the objective's panel copy failed");
+  if (nmd::objective_split_rank(c->rp) && !c->Pobj &&
+      (dalloc(&c->Pobj, nmd::split_work_floats(c->n, c->rp)) != hipSuccess ||
+       dalloc(&c->obj_nan, 1) != hipSuccess)) {
+    (void)hipGetLastError();  // tried again at the next call
+    dfree(c->Pobj);
+  }
+  if (c->Pobj) {
     const int nsub = objective_subs(c, nmd::split_rows_per_wg(c->rp), 32);
     HIP_TRY(c, nmd::launch_objective_split(c->A, c->m, c->B, c->n, sd.d_bounds, sd.nblk(), nsub,
                                            sd.d_rowptr, sd.d_idx, sd.d_val, c->rp, metrics, c->Pobj,
