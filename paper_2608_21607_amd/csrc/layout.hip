@@ -5,36 +5,39 @@
 
 namespace nmd {
 
-// Both panels in one launch: workgroups below `row_wgs` copy rows of W (m x r) into A (m x rp,
+// Both panels in one launch: units below `row_units` copy 256 elements of W (m x r) into A (m x rp,
 // zeros beyond r), the others 32 x 32 tiles of H (r x n) through LDS into B (n x rp).
 __global__ __launch_bounds__(256) void load_panels_kernel(const float* __restrict__ W, int64_t m,
                                                           const float* __restrict__ H, int64_t n,
                                                           int r, int rp, float* __restrict__ A,
-                                                          float* __restrict__ B, unsigned row_wgs,
-                                                          unsigned col_tiles) {
+                                                          float* __restrict__ B, int64_t row_units,
+                                                          int64_t col_tiles, int64_t units) {
   __shared__ float t[32][33];
-  if (blockIdx.x < row_wgs) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= m * rp) return;
-    const int64_t i = e / rp;
-    const int c = (int)(e - i * rp);
-    A[e] = c < r ? W[i * r + c] : 0.f;
-    return;
-  }
-  const unsigned g = blockIdx.x - row_wgs;
-  const int64_t j0 = (int64_t)(g % col_tiles) * 32;
-  const int c0 = (int)(g / col_tiles) * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 256 threads: 32 x 8
-  for (int k = ty; k < 32; k += 8) {
-    const int c = c0 + k;
-    const int64_t j = j0 + tx;
-    t[k][tx] = (c < r && j < n) ? H[(int64_t)c * n + j] : 0.f;
-  }
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int64_t j = j0 + k;
-    const int c = c0 + tx;
-    if (j < n && c < rp) B[j * rp + c] = t[tx][k];
+  for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    if (u < row_units) {
+      const int64_t e = u * 256 + threadIdx.x;
+      if (e >= m * rp) continue;
+      const int64_t i = e / rp;
+      const int c = (int)(e - i * rp);
+      A[e] = c < r ? W[i * r + c] : 0.f;
+      continue;
+    }
+    const int64_t g = u - row_units;
+    const int64_t j0 = (g % col_tiles) * 32;
+    const int c0 = (int)(g / col_tiles) * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 256 threads: 32 x 8
+    __syncthreads();  // the tile before has been read
+    for (int k = ty; k < 32; k += 8) {
+      const int c = c0 + k;
+      const int64_t j = j0 + tx;
+      t[k][tx] = (c < r && j < n) ? H[(int64_t)c * n + j] : 0.f;
+    }
+    __syncthreads();
+    for (int k = ty; k < 32; k += 8) {
+      const int64_t j = j0 + k;
+      const int c = c0 + tx;
+      if (j < n && c < rp) B[j * rp + c] = t[tx][k];
+    }
   }
 }
 
@@ -43,36 +46,39 @@ __global__ __launch_bounds__(256) void load_panels_kernel(const float* __restric
 __global__ __launch_bounds__(256) void store_panels_kernel(const float* __restrict__ A, int64_t m,
                                                            const float* __restrict__ B, int64_t n,
                                                            int r, int rp, float* __restrict__ W,
-                                                           float* __restrict__ H, unsigned row_wgs,
-                                                           unsigned col_tiles, const int* status,
-                                                           int* host_status) {
+                                                           float* __restrict__ H, int64_t row_units,
+                                                           int64_t col_tiles, int64_t units,
+                                                           const int* status, int* host_status) {
   __shared__ float t[32][33];
   if (blockIdx.x == 0 && threadIdx.x == 0 && host_status) {
     host_status[0] = status[0];
     host_status[1] = status[1];
   }
-  if (blockIdx.x < row_wgs) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= m * r) return;
-    const int64_t i = e / r;
-    const int c = (int)(e - i * r);
-    W[e] = A[i * rp + c];
-    return;
-  }
-  const unsigned g = blockIdx.x - row_wgs;
-  const int64_t j0 = (int64_t)(g % col_tiles) * 32;
-  const int c0 = (int)(g / col_tiles) * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int k = ty; k < 32; k += 8) {
-    const int64_t j = j0 + k;
-    const int c = c0 + tx;
-    t[k][tx] = (j < n && c < rp) ? B[j * rp + c] : 0.f;
-  }
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int c = c0 + k;
-    const int64_t j = j0 + tx;
-    if (c < r && j < n) H[(int64_t)c * n + j] = t[tx][k];
+  for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    if (u < row_units) {
+      const int64_t e = u * 256 + threadIdx.x;
+      if (e >= m * r) continue;
+      const int64_t i = e / r;
+      const int c = (int)(e - i * r);
+      W[e] = A[i * rp + c];
+      continue;
+    }
+    const int64_t g = u - row_units;
+    const int64_t j0 = (g % col_tiles) * 32;
+    const int c0 = (int)(g / col_tiles) * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    __syncthreads();  // the tile before has been read
+    for (int k = ty; k < 32; k += 8) {
+      const int64_t j = j0 + k;
+      const int c = c0 + tx;
+      t[k][tx] = (j < n && c < rp) ? B[j * rp + c] : 0.f;
+    }
+    __syncthreads();
+    for (int k = ty; k < 32; k += 8) {
+      const int c = c0 + k;
+      const int64_t j = j0 + tx;
+      if (c < r && j < n) H[(int64_t)c * n + j] = t[tx][k];
+    }
   }
 }
 
@@ -142,34 +148,30 @@ __global__ __launch_bounds__(1024) void sum_kernel(const double* __restrict__ pa
 
 static inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-// Grid of the panel copies: row workgroups, then 32 x 32 tiles of H.
-static bool panel_grid(int64_t row_elems, int64_t n, int rank, unsigned& row_wgs, unsigned& col_tiles,
-                       unsigned& total) {
-  const int64_t rw = (row_elems + 255) / 256, ct = (n + 31) / 32;
-  const int64_t all = rw + ct * ((rank + 31) / 32);
-  if (all > 0x7fffffffLL) return false;
-  row_wgs = (unsigned)rw;
-  col_tiles = (unsigned)ct;
-  total = (unsigned)all;
-  return true;
-}
+// The panel copies' units: 256 elements of the rows, then 32 x 32 tiles of H.  A launch holds fewer
+// than 2^32 threads, which both panels together may need more of (each alone had a launch before).
+struct PanelUnits {
+  int64_t rows, tiles, all;
+  unsigned wgs;
+  PanelUnits(int64_t row_elems, int64_t n, int rank)
+      : rows((row_elems + 255) / 256), tiles((n + 31) / 32), all(rows + tiles * ((rank + 31) / 32)),
+        wgs((unsigned)(all < (1 << 23) ? all : 1 << 23)) {}
+};
 
 hipError_t launch_load_panels(const float* W, int64_t m, const float* H, int64_t n, int r, int rp,
                               float* A, float* B, hipStream_t st) {
-  unsigned rw, ct, total;
-  if (!panel_grid(m * rp, n, rp, rw, ct, total)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(load_panels_kernel, dim3(total), dim3(256), 0, st, W, m, H, n, r, rp, A, B, rw,
-                     ct);
+  const PanelUnits u(m * rp, n, rp);
+  hipLaunchKernelGGL(load_panels_kernel, dim3(u.wgs), dim3(256), 0, st, W, m, H, n, r, rp, A, B, u.rows,
+                     u.tiles, u.all);
   return hipGetLastError();
 }
 
 hipError_t launch_store_panels(const float* A, int64_t m, const float* B, int64_t n, int r, int rp,
                                float* W, float* H, const int* status, int* host_status,
                                hipStream_t st) {
-  unsigned rw, ct, total;
-  if (!panel_grid(m * r, n, r, rw, ct, total)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(store_panels_kernel, dim3(total), dim3(256), 0, st, A, m, B, n, r, rp, W, H, rw,
-                     ct, status, host_status);
+  const PanelUnits u(m * r, n, r);
+  hipLaunchKernelGGL(store_panels_kernel, dim3(u.wgs), dim3(256), 0, st, A, m, B, n, r, rp, W, H,
+                     u.rows, u.tiles, u.all, status, host_status);
   return hipGetLastError();
 }
 
