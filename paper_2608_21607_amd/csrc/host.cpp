@@ -35,10 +35,6 @@ constexpr int kMaxSplits = 16;     // partial outputs of the dense kernel
 constexpr int64_t kSplitRows = 8192;  // at most this many panel rows per fp32 accumulation
 constexpr int64_t kTargetWgs = 2048;  // dense workgroups wanted per launch (256 CUs)
 constexpr int64_t kWgFixedRows = 32;  // per-workgroup set-up and write-back, in panel rows
-// A full step of the deterministic mode takes all blocks' sparse corrections in one launch, a wave
-// per row, where a row is short enough for one wave and the blocks few enough to walk.
-constexpr int64_t kRowsEntries = 512;
-constexpr int32_t kRowsBlocks = 32;
 constexpr int kObjSubMax = 16;        // sub-splits of a column block in the objective
 // Steps one call may enqueue: the device status word keeps step_id * 8 + flag in an int.
 constexpr int64_t kMaxStepsPerCall = int64_t{1} << 27;
@@ -620,6 +616,26 @@ int factor_run(nmd_ctx* c, bool wstep, const int32_t* blocks, int n, int first_s
   return NMD_OK;
 }
 
+// Whether a full step of the deterministic mode takes the sparse corrections of all n blocks in one
+// launch, a wave per row, instead of a launch per block, a team per row and block that has entries.
+// One launch saves 6.8 us for each of the others, and the row's own reads for all but one of its
+// blocks, but reads every row, empty ones too: 0.18, 0.36 and 0.66 ns a row at r_p = 16, 64 and 256.
+// Measured on both sides of the line, a sweep's two corrections, by rows / by blocks in us, four blocks:
+// 1M x 2000, r = 64 with 0.01 / 1 / 3 entries a row 361 / 55, 722 / 310, 877 / 523; 40000 x 20000, r =
+// 64 with 1 / 8 / 60 47 / 55, 61 / 91, 153 / 174, r = 256 with 0.05 / 1 / 8 / 30 57 / 54, 99 / 91, 163 /
+// 208, 324 / 354; 2000 x 2000 at any rank and density a quarter to two thirds of the time.
+// Where a row meets many entries of a block, the blocks' launches keep to a part of a panel that does
+// not fit an XCD's L2: 40000 x 20000 with 250 entries a row, r = 192 / 256 / 384 1607 / 1514, 2152 /
+// 1652, 3815 / 3509 (r = 128, 10 MB of panel 1389 / 1523; sixteen blocks, r = 256 2128 / 2229).
+bool sparse_by_rows(const Side& sd, int rp, int64_t rows, int32_t n) {
+  constexpr int32_t kBlocks = 32;    // walked in turn by the row's wave
+  constexpr int64_t kEntries = 512;  // of a row at most: one wave takes them
+  if (n < 2 || n > kBlocks || sd.max_row > kEntries || rows >= (int64_t{1} << 25)) return false;
+  const int64_t items = sd.item_off[n], entries = sd.entry_off[n];
+  if (entries > 16 * items && sd.other * rp > 3000000) return false;
+  return 6.8e-6 * (n - 1) + (0.15e-9 + 2.1e-12 * rp) * (double)(items - rows) > 0.0;
+}
+
 // One update step with the -G^-1 that factor_run formed for it.
 // `later`: the run's solve where the run's first step has to launch it, else nullptr.
 int factor_step(nmd_ctx* c, bool wstep, int32_t block, float eta, float gamma, int step_id,
@@ -639,12 +655,13 @@ int factor_step(nmd_ctx* c, bool wstep, int32_t block, float eta, float gamma, i
   const int64_t y_stride = rows * rp;
   if (ns * y_stride > c->ypart_floats)
     return fail(c, NMD_EDEVICE, "internal: partial-output buffer too small");
-  // At r_p >= 320 (fp32) the sparse correction runs beside the contraction, on its own stream, into
-  // its own buffer: it is bound by memory and needs no LDS, so its workgroups fill what the
-  // contraction leaves (125000 x 50000, r = 512 92.2 ms a sweep against 94.0 behind it; 40001 x
-  // 30011, r = 384 the same).  At r_p <= 256 the correction beside it slowed it by more than the
-  // correction's own time (graph sweep 202.5 -> 204.5 ms); there it runs after the contraction, on
-  // the same stream, added in place to the first partial output.  X and P are final here.
+  // At r_p >= 320 (without the bf16x3 option) the sparse correction runs beside the contraction, on its
+  // own stream, into its own buffer: it is bound by memory and needs no LDS, so its workgroups fill
+  // what the contraction leaves (125000 x 50000, r = 512 92.2 ms a sweep against 94.0 behind it, with
+  // a shorter contraction; 40001 x 30011, r = 384 the same).  At r_p <= 256 it gains nothing (139255^2,
+  // r = 256 145.7 ms beside it and 145.6 behind; 34814^2, r = 200 23.5 and 23.7): there it runs after the
+  // contraction, on the same stream, added in place to the first partial output.  X and P are final
+  // here.
   const bool beside = !c->Pbx && rp >= 320;
   if (beside) {
     HIP_TRY(c, hipEventRecord(c->ev_cfork, st));
@@ -682,7 +699,7 @@ int factor_step(nmd_ctx* c, bool wstep, int32_t block, float eta, float gamma, i
   const int32_t b0 = block >= 0 ? block : 0;
   const int32_t b1 = block >= 0 ? block + 1 : sd.nblk();
   if (beside) HIP_TRY(c, nmd::launch_zero(c->Ysp, rows * rp, cs));
-  const bool by_rows = b1 - b0 > 1 && b1 - b0 <= kRowsBlocks && sd.max_row <= kRowsEntries;
+  const bool by_rows = block < 0 && sparse_by_rows(sd, rp, rows, b1);
   bool solve_too = later && later->sb.n > 0;
   auto solve_sparse = [&](const nmd::SparseWork& w) {
     return nmd::launch_solve_sparse(later->P, later->sb, c->r, rp, c->Gpart, later->nchunks,
@@ -697,8 +714,8 @@ int factor_step(nmd_ctx* c, bool wstep, int32_t block, float eta, float gamma, i
              8.0 * nz + (beside ? 8.0 : 12.0) * rows * c->r + 4.0 * blk * c->r);
     HIP_TRY(c, nmd::launch_sparse_rows(sd.d_rowptr, b1 - b0, rows, sd.d_idx, sd.d_val, X, P, rp, Ycorr,
                                        beside ? 0 : 1, cs));
-  } else
-  for (int32_t b = b0; b < b1; ++b) {
+  }
+  for (int32_t b = b0; b < b1 && !by_rows; ++b) {
     const int64_t ni = sd.item_off[b + 1] - sd.item_off[b];
     const int64_t nsp = sd.split_off[b + 1] - sd.split_off[b];
     const int64_t nz = sd.entry_off[b + 1] - sd.entry_off[b];

@@ -10,6 +10,7 @@ from oracle import salsa
 from workloads import gen
 
 import paper_2608_21607_amd as nmd
+from paper_2608_21607_amd import nmd as binding
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +62,26 @@ def test_full_step_sparse_rows(r, heavy):
     counts = np.diff(S[0])
     assert (counts.max() > 512) == (heavy > 0)
     run(m, n, r, 330, 400, S, "deterministic", 7)
+
+
+# many rows without entries; a few entries in every row; many entries a row against a long panel
+@pytest.mark.parametrize("m,n,r,blocks,per,by_rows", [
+    (300_000, 200, 20, 4, 0.01, False), (300_000, 200, 20, 4, 3.0, True), (3000, 900, 20, 3, 0.01, True),
+    (3000, 900, 150, 30, 5.0, True), (3000, 900, 150, 33, 5.0, False), (700, 30_000, 128, 4, 100.0, False)])
+def test_full_step_sparse_route(m, n, r, blocks, per, by_rows):
+    """One launch for all blocks only where it is the faster: the W-step's corrections are one launch by
+    rows and one per block otherwise, and the sweep is the oracle's either way."""
+    print("[case]", m, n, r, blocks, per, flush=True)
+    g = np.random.default_rng(m + r)
+    keys = np.unique(np.concatenate([g.integers(0, m * n, int(m * per)), (np.arange(n) % m) * n + np.arange(n)]))
+    row_ptr = np.zeros(m + 1, np.int64)
+    row_ptr[1:] = np.cumsum(np.bincount(keys // n, minlength=m))
+    S = (row_ptr, (keys % n).astype(np.int32), g.uniform(0.5, 2.0, keys.size).astype(np.float32))
+    bn = -(-n // blocks)
+    run(m, n, r, m, bn, S, "deterministic", 5)
+    ctx = nmd.Context(m, n, r, m, bn, seed=3, mode="deterministic", eta=0.5, flags=binding.FLAG_TIMING)
+    ctx.set_sparse_csr(*S)
+    W0, H0 = gen.sign_constrained_init(m, n, r, 1.0, 5)
+    ctx.sweep(dev(W0), dev(H0), 1)
+    # the H-step has one block
+    assert ctx.kernel_timing(1)["launches"] == 1 + (1 if by_rows else blocks)
