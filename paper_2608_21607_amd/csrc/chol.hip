@@ -697,39 +697,27 @@ hipError_t launch_solve_sparse(const float* P, const SolveBatch& sb, int r, int 
   return hipGetLastError();
 }
 
-int64_t chol_work_doubles(int rp) {
-  const int NB = rp < 64 ? rp : 64;
-  return 3 * (int64_t)rp * rp + (int64_t)(rp / NB) * NB * NB;
-}
+constexpr int kBlock = 64;  // columns of a block, r_p >= 128 (below, launch_solve_small)
+
+int64_t chol_work_doubles(int rp) { return 3 * (int64_t)rp * rp + (int64_t)rp * kBlock; }
 
 hipError_t launch_chol_inverse(const double* G, double* work, int rp, int* status,
                                const SolveBatch& sb, double** result, hipStream_t st) {
-  if (sb.n < 1 || sb.n > kSolveBatch) return hipErrorInvalidValue;
-  const int NB = rp < 64 ? rp : 64;
-  const int nb = rp / NB;
+  if (sb.n < 1 || sb.n > kSolveBatch || rp % kBlock) return hipErrorInvalidValue;
+  const int nb = rp / kBlock;
   const int64_t per = chol_work_doubles(rp);
   const unsigned nm = (unsigned)sb.n;
-#define CHOL_NB(B)                                                                           \
-  case B: {                                                                                  \
-    for (int k = 0; k < nb; ++k) {                                                           \
-      hipLaunchKernelGGL((chol_col_kernel<B>), dim3(nb - k, nm), dim3(kThreads), 0, st, G, work, \
-                         per, rp, k, status, sb);                                            \
-      hipError_t e = hipGetLastError();                                                      \
-      if (e != hipSuccess) return e;                                                         \
-    }                                                                                        \
-    hipLaunchKernelGGL((chol_trinv_kernel<B>), dim3(nb, nm), dim3(kThreads), 0, st, work, per, \
-                       rp);                                                                  \
-    hipError_t e = hipGetLastError();                                                        \
-    if (e != hipSuccess) return e;                                                           \
-    hipLaunchKernelGGL((chol_gram_kernel<B>), dim3(nb * (nb + 1) / 2, nm), dim3(kThreads), 0, st, \
-                       work, per, rp, status, sb);                                           \
-    break;                                                                                   \
+  for (int k = 0; k < nb; ++k) {
+    hipLaunchKernelGGL((chol_col_kernel<kBlock>), dim3(nb - k, nm), dim3(kThreads), 0, st, G, work, per,
+                       rp, k, status, sb);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  switch (NB) {
-    CHOL_NB(64)
-    default: return hipErrorInvalidValue;
-  }
-#undef CHOL_NB
+  hipLaunchKernelGGL((chol_trinv_kernel<kBlock>), dim3(nb, nm), dim3(kThreads), 0, st, work, per, rp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((chol_gram_kernel<kBlock>), dim3(nb * (nb + 1) / 2, nm), dim3(kThreads), 0, st, work,
+                     per, rp, status, sb);
   for (int b = 0; b < sb.n; ++b) result[b] = Work(work, per, b, rp).Gneg;
   return hipGetLastError();
 }

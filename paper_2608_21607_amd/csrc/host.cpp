@@ -264,7 +264,11 @@ int64_t nsplit_for(int64_t rows, int64_t blk, int64_t rw, int64_t slots) {
 // about 40 rows, and a partial output (written here, read by the apply) 0.4 rows per row tile.
 // Measured per sweep, splits 2 / 3 / 4 / 6 / 8: 139255^2, r = 256 152 / 149 / 147 / 149 / 153 ms;
 // 34814^2, r = 200, guarded 27.0 / 26.7 / 26.6 / 26.9 / 29.1; 40001 x 30011, r = 384 15.8 / 15.7 / 15.7 /
-// 16.2 / 16.9; 125000 x 50000, r = 512 140 / 134 / 130 / 126 / 132.
+// 16.2 / 16.9; 125000 x 50000, r = 512 140 / 134 / 130 / 126 / 132.  Off those shapes, its own choice and
+// the best of the counts: 5000 x 4000, r = 192 1.86, 1.80 ms; 12000 x 11000, r = 256 2.72, 2.70 (one
+// range leaves the solve beside it room: 2.28); 20000 x 15000, r = 128 1.98, 1.76; 60000 x 8000, r =
+// 300 10.2, 9.3; 90000 x 30000, r = 448 37.5, 35.6.  Counting whole rounds and 80 rows a workgroup gave
+// 1.84, 2.73, 1.70, 9.7 and 36.7 there, but 152 ms at the first shape.
 int64_t nsplit_split(int64_t rows, int64_t blk, int64_t rw, int64_t slots) {
   const int64_t tiles = (rows + rw - 1) / rw;
   const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, blk / 32));
@@ -286,8 +290,10 @@ int64_t nsplit_split(int64_t rows, int64_t blk, int64_t rw, int64_t slots) {
 // of its ranks): the rounds of workgroups, each with its panel rows and about 60 rows for its
 // set-up, and for every split the partial output, written here and read by the apply (8 bytes an
 // element at 4.5 TB/s).  Measured per fit, splits 1 / 2 / 4 / 8 / 16: 32768^2, r = 64 (4096-row
-// panels; two fill every CU once) 4.25 / 2.97 / 3.60 / 3.83 / 4.29 ms; 5003 x 2999, r = 40 1.87 /
-// 1.55 / 1.37 / 1.35 / 1.46 ms; 4096^2, r = 3 998 / 607 / 415 / 329 / 301 us.
+// panels; two fill every CU once) 5.22 / 3.55 / 4.12 / 4.30 / 4.58 ms; 5003 x 2999, r = 40 1.74 /
+// 1.31 / 1.12 / 1.07 / 1.20 ms; 4096^2, r = 3 1139 / 658 / 426 / 316 / 275 us; its own choice and the best
+// of nine counts: 60000 x 50000, r = 16 1.87, 1.94 ms; 20000 x 15000, r = 30 1.11, 1.16; 9001 x 7003, r =
+// 48 0.67, 0.66; 30000 x 3000, r = 64 1.41, 1.46; 100000 x 20000, r = 50 5.15, 5.16.
 int64_t nsplit_small(int64_t rows, int64_t blk, int64_t rw, int64_t rp, int64_t slots) {
   const int64_t tiles = (rows + rw - 1) / rw;
   const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, blk / 16));

@@ -16,11 +16,11 @@ namespace nmd {
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------- Gram --
-// grid (npairs, nchunks); tile T = min(64, rp).  A workgroup accumulates the T x T tile
+// grid (npairs, nchunks); tile T = 64, rp a multiple of it.  A workgroup accumulates the T x T tile
 // (ti, tj), ti <= tj, of P^T P over one chunk of panel rows on fp64 MFMA: wave w owns the
 // 16-row block w of the tile; srcA lane l = P[k + l/16][ti T + 16 w + l%16], srcB lane l =
 // P[k + l/16][tj T + 16 cb + l%16] (fp32 inputs widened exactly to fp64).
-template <int T>
+constexpr int kGramTile = 64;
 __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Pbase, SolveBatch sb,
                                                    int rp, double* __restrict__ Gpart_all,
                                                    int nchunks) {
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Pba
   const float* __restrict__ P = Pbase + sb.j0[blockIdx.z] * rp;
   const int64_t blk = sb.blk[blockIdx.z];
   double* __restrict__ Gpart = Gpart_all + (int64_t)blockIdx.z * nchunks * rp * rp;
-  constexpr int NCB = T / 16;
+  constexpr int T = kGramTile, NCB = T / 16;
   constexpr int KB = 64;
   __shared__ float si[KB][T + 1];
   __shared__ float sj[KB][T + 1];
@@ -43,7 +43,6 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Pba
   const int64_t k0 = (int64_t)c * blk / nchunks, k1 = (int64_t)(c + 1) * blk / nchunks;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int q = lane >> 4, l16 = lane & 15;
-  const bool active = wave < NCB;
   doublex4 acc[NCB];
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) acc[cb] = doublex4{0.0, 0.0, 0.0, 0.0};
@@ -61,18 +60,15 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Pba
       sj[kk][col] = vj;
     }
     __syncthreads();
-    if (active) {
-      for (int kk = 0; kk < KB; kk += 4) {
-        const double av = (double)si[kk + q][16 * wave + l16];
+    for (int kk = 0; kk < KB; kk += 4) {
+      const double av = (double)si[kk + q][16 * wave + l16];
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          const double bv = (double)sj[kk + q][16 * cb + l16];
-          acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[cb], 0, 0, 0);
-        }
+      for (int cb = 0; cb < NCB; ++cb) {
+        const double bv = (double)sj[kk + q][16 * cb + l16];
+        acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[cb], 0, 0, 0);
       }
     }
   }
-  if (!active) return;
   double* out = Gpart + (int64_t)c * rp * rp;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb)
@@ -83,8 +79,9 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Pba
 
 // G[i][j] = sum over chunks of the upper-tile partial (mirrored), identity on padded diagonal.
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ Gpart_all,
-                                                          int nchunks, int r, int rp, int T,
+                                                          int nchunks, int r, int rp,
                                                           double* __restrict__ G_all) {
+  constexpr int T = kGramTile;
   const double* __restrict__ Gpart = Gpart_all + (int64_t)blockIdx.y * nchunks * rp * rp;
   double* __restrict__ G = G_all + (int64_t)blockIdx.y * rp * rp;
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -101,17 +98,17 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
 hipError_t launch_gram(const float* P, const SolveBatch& sb, int r, int rp, double* Gpart,
                        int nchunks, double* G, hipStream_t st) {
   if (sb.n < 1 || sb.n > kSolveBatch) return hipErrorInvalidValue;
-  constexpr int T = 64;
+  constexpr int T = kGramTile;
   if (rp % T) return hipErrorInvalidValue;  // smaller ranks: launch_solve_small
   const int nt = rp / T;
   const int npairs = nt * (nt + 1) / 2;
   const dim3 grid(npairs, nchunks, sb.n);
-  hipLaunchKernelGGL((gram_kernel<T>), grid, dim3(256), 0, st, P, sb, rp, Gpart, nchunks);
+  hipLaunchKernelGGL(gram_kernel, grid, dim3(256), 0, st, P, sb, rp, Gpart, nchunks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t n = (int64_t)rp * rp;
   hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((n + 255) / 256), sb.n), dim3(256), 0, st,
-                     Gpart, nchunks, r, rp, T, G);
+                     Gpart, nchunks, r, rp, G);
   return hipGetLastError();
 }
 

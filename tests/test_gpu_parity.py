@@ -417,18 +417,18 @@ def test_stochastic_planted_reduced(eta, mom):
     assert ctx.schedule(0) == schedule.sweep_schedule(p.seed, 0, R, C, True)
 
 
-@pytest.mark.parametrize("case", ["r64_fused", "r128_multi", "r320_fused"])
+@pytest.mark.parametrize("case", ["r64", "r128", "r320"])
 def test_long_runs_of_same_side_steps(case):
     """Uneven block grids, so that the schedule has runs of more than eight H-steps (21 or 20
     row blocks against 2 or 1 column blocks): their solves are formed in batches of up to
-    eight, by the single-workgroup form at r_p = 64 and 320 and the multi-launch form at 128.
+    eight, in one launch with the Gram matrices at r_p = 64, a launch per block column at 128 and 320.
     One sweep, momentum 0.9, against the oracle."""
-    if case == "r320_fused":
+    if case == "r320":
         p = gen.config(4, scale=0.1)  # 13926 x 13926 graph-like counts
         r, p.block_m, p.block_n = 320, 700, p.n
     else:
         p = gen.config(3, scale=0.125)  # 4096 x 4096 planted
-        r, p.block_m, p.block_n = (64 if case == "r64_fused" else 128), 200, 2048
+        r, p.block_m, p.block_n = (64 if case == "r64" else 128), 200, 2048
     if r != p.r:
         p.r = r
         p.W0, p.H0 = gen.sign_constrained_init(p.m, p.n, r, float(p.val.mean()), 1003)
