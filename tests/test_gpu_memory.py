@@ -22,7 +22,8 @@ def test_little_memory_left():
     def run(then=lambda: None):
         ctx = nmd.Context(m, n, r, m, n, seed=1, mode="stochastic")
         ctx.set_sparse_csr(*S)
-        W, H = W0.clone(), H0.clone()
+        W.copy_(W0)
+        H.copy_(H0)
         before = torch.cuda.mem_get_info()[0]
         ctx.run_steps(W, H, [1])
         used = before - torch.cuda.mem_get_info()[0]
@@ -30,22 +31,28 @@ def test_little_memory_left():
         then()
         again = ctx.objective(W, H)
         ctx.close()
-        return W, f, again, used
+        return W.clone(), f, again, used
 
-    W, f, _, used = run()
+    W, H = W0.clone(), H0.clone()
+    run()  # what is allocated once (code objects, streams) is there when the second run is measured
+    W1, f, _, used = run()
     room = used - 300_000_000
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
-    spare = W0.numel() * 8 + H0.numel() * 8  # the clones of the next run
-    keep = torch.cuda.mem_get_info()[0] - room - spare
     print(f"[case] a context takes {used >> 20} MB, {room >> 20} MB are left", flush=True)
-    filler = [torch.empty(keep, dtype=torch.uint8, device="cuda")]
+    filler = []
+    for _ in range(8):  # a first piece may find cached memory that the free count does not hold
+        over = torch.cuda.mem_get_info()[0] - room
+        if over < 16_000_000:
+            break
+        filler.append(torch.empty(over, dtype=torch.uint8, device="cuda"))
+    assert torch.cuda.mem_get_info()[0] < room + 16_000_000
 
     def free():
         filler.clear()
         torch.cuda.empty_cache()
 
     W2, f2, f3, used2 = run(free)
-    assert used2 < used  # the copy was left out
-    assert float((W2 - W).norm() / W.norm()) < 1e-5
+    assert used2 < used - 200_000_000  # the copy was left out
+    assert float((W2 - W1).norm() / W1.norm()) < 1e-5
     assert abs(f2 / f - 1) < 1e-7 and abs(f3 / f - 1) < 1e-7
