@@ -1,7 +1,7 @@
 // Three-term bf16 splits: fp32 operands on bf16 MFMA without losing a bit.
 //
 // x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m: 24 significant bits in three
-// times eight, exact for every x of in_split_range.  A product x p is taken as
+// times eight, exact for every x within Range.  A product x p is taken as
 //   h h + (h m + m h + m m + h l + l h),
 // the terms in brackets in an accumulator of their own; the terms left out (m l, l m, l l) are
 // below 2^-24 of |x p| (rms 2^-27, half a percent of what rounding one fp32 product costs), relative to each
